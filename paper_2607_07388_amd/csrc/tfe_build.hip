@@ -3,39 +3,32 @@
 // frequency; n-gram extraction dominates the construction time reported in
 // the evaluation).
 //
-// Steps, all on the device:
-//   1. key formation: every window of n tokens becomes one 64-bit key, the
-//      tokens in 18-bit fields, oldest in the highest field, so that key
-//      order is tuple order; a window with a token outside [0, vocab) gets
-//      a mark above every valid key: vocab in the oldest field when vocab <
-//      2^18 (the keys keep 18 n bits), else 2^(18 n) (formed by the first
-//      pass of the sort, from the tokens);
-//   2. LSD radix sort of the keys, 9-bit digits (an 18-bit token field is
-//      two digits) over the key bits (the valid keys end up first; a binary
-//      search counts them): per pass a digit histogram per tile (4096 keys;
-//      3072 with a payload), one exclusive scan of the digit-major
-//      histogram, and a stable scatter
-//      (each wave ranks its keys with ballot-based digit matching, the tile
-//      is reordered in LDS and written out in digit runs);
-//   3. run-length count: per-block counts of run starts, their scan, the
-//      starts written at their ranks into a unique-key array; a run's count
-//      is the distance to the next start;
-//   4. selection of ranks [0, skip + top): the (skip+top)-th largest count
-//      c* from a histogram of the small counts (a radix select over the
-//      counts when c* is large), then an order-preserving compaction of the
-//      runs with count > c* and the first needed ones with count == c* (key
-//      order = tuple order, which breaks the ties);
-//   5. ranking: a stable radix sort of the selected runs by descending count
-//      (payload: the run index), which keeps tuple order among equal counts;
-//   6. ranks [skip, skip + top) are unpacked into tuples and counts.
-// 4-grams need 72 key bits: the three newest tokens form the low word and
-// the oldest token the high word; the LSD sort runs over the low word (high
-// word as a 32-bit payload) and then stably over the high word.
+// Only the selected n-grams have to come out in order, so nothing else is
+// sorted: the windows are grouped by hash, counted in LDS, and the few that
+// are selected are ranked.  Steps, all on the device:
+//   1. every window of n valid tokens becomes a partition number (up to 12
+//      bits) and a remainder word (32 bits for n <= 2, else 64) that
+//      together determine the tuple (a bijection, so remainders are compared
+//      instead of tuples); a histogram per tile, one exclusive scan and a
+//      scatter group the remainders by partition, in no particular order;
+//   2. each partition's remainders are counted in an LDS hash table by one
+//      block (slices of a partition that heavy repetition made long are
+//      counted by several blocks, whose partial counts a second launch adds
+//      up; a table that fills up is retried on halves of the remainders);
+//   3. the (skip + top)-th largest count c* from a histogram of the counts;
+//   4. the n-grams with count >= c* become records that compare in rank
+//      order: count descending, then tuple (when far more n-grams have
+//      count c* than are needed, a radix select over their tuples first
+//      finds the last one needed);
+//   5. the records are ranked by one bucket sort (splitters from a sample,
+//      LDS sorts), which writes ranks [skip, skip + top) as tuples and
+//      counts; rankings of millions of records take a radix sort instead.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/tfe.h"
@@ -44,49 +37,36 @@
 namespace tfe {
 namespace {
 
-// Radix tiles: the scatter runs 512 threads per tile (one per digit), 8
-// keys per thread for keys alone (4096 keys: 52 KB of LDS with the 512-bin
-// counts, so three tiles share a CU and one tile's ranking overlaps the
-// others' memory traffic) and 6 with a 64-bit payload (68 KB, two tiles per
-// CU).  Measured on MI355X with 8-bit digits for keys alone: 5120-key tiles
-// beat 4096 (2.71 against 2.73 ms for the 2^26-token 2-gram table) and 8192
-// (2.83 ms), whose 74 KB allow two tiles per CU; with 9-bit digits the 36-bit
-// 2-gram keys take four passes instead of five (2.50 ms).  The histogram of
-// a tile is counted by 1024 threads.
-constexpr int kTileThreads = 512;
-constexpr int kTileWaves = kTileThreads / 64;
-constexpr int kHistThreads = 1024;
-template <class K, bool PAIRS, class V>
-constexpr int tile_items() { return (sizeof(K) + (PAIRS ? sizeof(V) : 0)) > 8 ? 6 : 8; }
-template <class K, bool PAIRS, class V>
-constexpr int tile_keys() { return kTileThreads * tile_items<K, PAIRS, V>(); }
-constexpr int kMinTile = kTileThreads * 6;  // smallest tile: sizes the histogram matrix
-// Radix digits: 9 bits (512 bins), so that 18-bit token fields take two
-// digits each.
-constexpr int kDigitBits = 9;
-constexpr uint32_t kBins = 1u << kDigitBits;
-static_assert(kBins <= (uint32_t)kTileThreads, "one scatter thread per digit");
 constexpr int kScanThreads = 1024;
 constexpr int kScanItems = 16;
 constexpr int kScanBlock = kScanThreads * kScanItems;
 
-// ---- 1. keys -----------------------------------------------------------------
+// ---- 1. windows -> partitions ---------------------------------------------------
 
-// One key per window, in window order (no compaction: the sort moves the
-// invalid windows, marked with a key just above every valid one, to the end).
-// The keys are formed from the tokens by the first radix pass itself.
+constexpr int kPartThreads = 1024;
+constexpr int kMinPartBits = 9;   // keeps 4-gram remainders below 2^63
+constexpr int kMaxPartBits = 12;
+constexpr uint32_t kMaxParts = 1u << kMaxPartBits;
+constexpr uint32_t kTok = 0x3FFFFu;  // token fields are 18 bits
+
 struct TokSrc {
   const int32_t* tok;
   int n;
   int32_t vocab;
-  uint64_t mark;   // key of an invalid window: just above every valid key
-  uint32_t mark4;  // 4-grams: high word of an invalid window
+  int pbits;  // log2 of the number of partitions
 };
 
-// Key sources: the key array, windows of 1, 2 or 3 tokens (the source is
-// the window length, known at compile time so that the token loads of all
-// of a thread's windows are in flight together), or 4-gram words.
-enum { kSrcKeys = 0, kSrcNgram4 = 4 };
+// Remainder word of an n-gram.
+template <int NG>
+using Rem = typename std::conditional<(NG <= 2), uint32_t, uint64_t>::type;
+
+// Windows per scatter thread and tile.  32-bit remainders: 14336 windows
+// (57 KB of LDS with their staged tokens, 73 KB with the 2048-bin counts: two
+// tiles per CU), 7 per partition and tile on average; 64-bit ones: 8192.
+template <int NG>
+constexpr int part_items() { return NG <= 2 ? 14 : 8; }
+template <int NG>
+constexpr int part_tile() { return kPartThreads * part_items<NG>(); }
 
 // Tokens a tile of windows [w0, w0 + TILE) needs: [w0, w0 + TILE + 3),
 // clipped to the stream (n windows of `ts.n` tokens: n + ts.n - 1 tokens),
@@ -120,64 +100,73 @@ __device__ __forceinline__ void stage_tokens(const TokSrc& ts, uint64_t n, uint6
   }
 }
 
-// Key of the window starting at staged token j (NG <= 3 tokens, oldest in
-// the highest field); an invalid window gets ts.mark.  4-grams: 72 key bits
-// in two words, lo = the three newest tokens (54 bits) and, as the payload,
-// hi = the oldest token, or ts.mark4 for an invalid window.
+// Radix tile of this block.  Workgroups are dispatched round-robin over the
+// 8 XCDs (each with its own L2); giving every XCD a contiguous range of
+// tiles keeps the 32 tiles that share a 128-byte line of the digit-major
+// histogram matrix on one XCD, so each line is written and read through
+// one L2 instead of eight.  A bijection of [0, G) for any G.
+__device__ __forceinline__ uint32_t xcd_tile(uint32_t b, uint32_t G) {
+  const uint32_t q = G >> 3, r = G & 7u, x = b & 7u;
+  return x * q + min(x, r) + (b >> 3);
+}
+
+
+// Hash of the tokens after the oldest one (18 bits).  24-bit multiplies run
+// at full rate.
+__device__ __forceinline__ uint32_t tail_hash(uint32_t t1, uint32_t t2, uint32_t t3) {
+  uint32_t h = __umul24(t1, 0xC2B2ADu) + __umul24(t2, 0x9E3779u) + __umul24(t3, 0x85EBCBu);
+  h ^= h >> 16;
+  h = __umul24(h & 0xFFFFFFu, 0xD35A2Du);
+  return h >> 14;
+}
+
+// The oldest token is scrambled by an odd multiplier modulo 2^18, which kMixInv
+// undoes, and masked with the hash of the others: m's top bits are the
+// partition, its other bits and the other tokens the remainder.
+constexpr uint32_t kMix = 0x2E5B5u;
+constexpr uint32_t mix_inverse() {
+  uint32_t x = kMix;  // Newton's iteration: x kMix = 1 modulo 8, 64, ..., 2^18
+  for (int i = 0; i < 4; ++i) x *= 2u - kMix * x;
+  return x & kTok;
+}
+constexpr uint32_t kMixInv = mix_inverse();
+static_assert(((kMix * kMixInv) & kTok) == 1u, "inverse modulo 2^18");
+
+// Partition and remainder of the window t[0 .. NG) (oldest first); false if
+// a token lies outside [0, vocab).
 template <int NG>
-__device__ __forceinline__ uint64_t ngram_key_lds(const int32_t* s, uint32_t j,
-                                                  const TokSrc& ts) {
-  uint64_t key = 0;
+__device__ __forceinline__ bool split_window(const int32_t* t, const TokSrc& ts, uint32_t* part,
+                                             Rem<NG>* rem) {
+  uint32_t x[4] = {0u, 0u, 0u, 0u};
   bool ok = true;
 #pragma unroll
   for (int q = 0; q < NG; ++q) {
-    const int32_t t = s[j + q];
-    ok = ok && t >= 0 && t < ts.vocab;
-    key = (key << 18) | (uint64_t)(uint32_t)(t & 0x3FFFF);
+    x[q] = (uint32_t)t[q];
+    ok = ok && x[q] < (uint32_t)ts.vocab;
   }
-  return ok ? key : ts.mark;
-}
-
-template <int SRC, class K>
-__device__ __forceinline__ K key_at_lds(const int32_t* s, uint32_t j, const TokSrc& ts) {
-  if (SRC == kSrcNgram4) {
-    uint64_t key = 0;
+  uint32_t m = __umul24(x[0] & kTok, kMix) & kTok;
+  if (NG > 1) m ^= tail_hash(x[1] & kTok, x[2] & kTok, x[3] & kTok);
+  const int low = 18 - ts.pbits;
+  *part = m >> low;
+  Rem<NG> r = (Rem<NG>)(m & ((1u << low) - 1u));
 #pragma unroll
-    for (int q = 1; q < 4; ++q) key = (key << 18) | (uint64_t)(uint32_t)(s[j + q] & 0x3FFFF);
-    return (K)key;
-  }
-  return (K)ngram_key_lds<(SRC >= 1 && SRC <= 3) ? SRC : 1>(s, j, ts);
+  for (int q = 1; q < NG; ++q) r = (r << 18) | (Rem<NG>)(x[q] & kTok);
+  *rem = r;
+  return ok;
 }
 
-__device__ __forceinline__ uint64_t val4_at_lds(const int32_t* s, uint32_t j, const TokSrc& ts) {
-  bool ok = true;
+// The tuple of a remainder.
+template <int NG>
+__device__ __forceinline__ void join_window(uint32_t part, Rem<NG> rem, int pbits, uint32_t* x) {
+  x[0] = x[1] = x[2] = x[3] = 0u;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) ok = ok && s[j + q] >= 0 && s[j + q] < ts.vocab;
-  return ok ? (uint64_t)(uint32_t)s[j] : (uint64_t)ts.mark4;
-}
-
-// Number of sorted keys below the invalid-window mark (one thread: binary
-// search).
-__global__ void k_count_valid(const uint64_t* keys, uint64_t nwin, uint64_t mark,
-                              unsigned long long* count) {
-  uint64_t lo = 0, hi = nwin;
-  while (lo < hi) {
-    const uint64_t mid = lo + (hi - lo) / 2;
-    if (keys[mid] < mark) lo = mid + 1;
-    else hi = mid;
+  for (int q = NG - 1; q >= 1; --q) {
+    x[q] = (uint32_t)rem & kTok;
+    rem >>= 18;
   }
-  *count = lo;
-}
-
-__global__ void k_count_valid_hi(const uint32_t* hi, uint64_t nwin, uint32_t mark,
-                                 unsigned long long* count) {
-  uint64_t lo = 0, top = nwin;
-  while (lo < top) {
-    const uint64_t mid = lo + (top - lo) / 2;
-    if (hi[mid] < mark) lo = mid + 1;
-    else top = mid;
-  }
-  *count = lo;
+  uint32_t m = (part << (18 - pbits)) | (uint32_t)rem;
+  if (NG > 1) m ^= tail_hash(x[1], x[2], x[3]);
+  x[0] = __umul24(m, kMixInv) & kTok;
 }
 
 // ---- device-wide exclusive scan of uint32 (totals below 2^32) ----------------
@@ -223,29 +212,6 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const uint32_t* in
   (void)block_scan_excl<kScanThreads>(s, s_wave, &tot);
   if (threadIdx.x == 0) part[blockIdx.x] = tot;
 }
-
-// Exclusive scan of the block sums in one block (nb <= kScanBlock), and
-// their total: the run count places its starts with it.
-__global__ __launch_bounds__(kScanThreads) void k_scan_partials(uint32_t* part, uint32_t nb,
-                                                                uint32_t* total) {
-  __shared__ uint32_t s_wave[kScanThreads / 64];
-  uint32_t v[kScanItems];
-  uint32_t s = 0;
-  for (int k = 0; k < kScanItems; ++k) {
-    const uint32_t i = threadIdx.x * kScanItems + k;
-    v[k] = i < nb ? part[i] : 0u;
-    s += v[k];
-  }
-  uint32_t tot;
-  uint32_t run = block_scan_excl<kScanThreads>(s, s_wave, &tot);
-  for (int k = 0; k < kScanItems; ++k) {
-    const uint32_t i = threadIdx.x * kScanItems + k;
-    if (i < nb) part[i] = run;
-    run += v[k];
-  }
-  if (threadIdx.x == 0 && total) *total = tot;
-}
-
 // Inclusive sum over the lanes up to this one: DPP shifts within each
 // 16-lane row, then the totals of the rows below (read out as scalars).
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
@@ -307,21 +273,794 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(const uint32_t* in, 
   }
 }
 
-// ---- 2. stable LSD radix sort (9-bit digits) --------------------------------
+// Windows of one tile per partition.
+template <int NG, uint32_t PMAX>
+__global__ __launch_bounds__(kPartThreads) void k_part_hist(TokSrc ts, uint64_t nwin,
+                                                            uint32_t* hist, uint32_t ntiles) {
+  constexpr int IT = part_items<NG>(), TILE = part_tile<NG>();
+  __shared__ uint32_t cnt[PMAX];
+  __shared__ int32_t s_tok[TILE + 4];
+  const uint32_t P = 1u << ts.pbits;
+  const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
+  const uint64_t base = (uint64_t)tile * TILE;
+  for (uint32_t e = threadIdx.x; e < P; e += kPartThreads) cnt[e] = 0u;
+  stage_tokens<TILE, kPartThreads>(ts, nwin, base, s_tok);
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < IT; ++r) {
+    const uint32_t j = (uint32_t)r * kPartThreads + threadIdx.x;
+    uint32_t part;
+    Rem<NG> rem;
+    const bool ok = split_window<NG>(s_tok + j, ts, &part, &rem);
+    if (ok && base + j < nwin) atomicAdd(&cnt[part], 1u);
+  }
+  __syncthreads();
+  for (uint32_t e = threadIdx.x; e < P; e += kPartThreads) hist[(size_t)e * ntiles + tile] = cnt[e];
+}
+
+// Scatter of one tile.  The order inside a partition is free, so a window's
+// place among the tile's windows of its partition is what its LDS atomic
+// returns; the remainders are regrouped in LDS and each partition's run is
+// written by a few consecutive lanes (then by whole waves, for the runs
+// that heavy repetition made long).
+template <int NG, uint32_t PMAX>
+__global__ __launch_bounds__(kPartThreads) void k_part_scatter(TokSrc ts, uint64_t nwin,
+                                                               const uint32_t* offs,
+                                                               uint32_t ntiles, Rem<NG>* out) {
+  using K = Rem<NG>;
+  constexpr int IT = part_items<NG>(), TILE = part_tile<NG>();
+  constexpr int PER = PMAX / kPartThreads;
+  constexpr int LG = NG <= 2 ? 8 : 4;  // lanes per run
+  __shared__ K buf[TILE + (sizeof(K) == 4 ? 4 : 0)];  // the staged tokens, then the remainders
+  __shared__ uint32_t loc[PMAX + 1], dlt[PMAX];
+  __shared__ uint32_t s_wave[kPartThreads / 64];
+  static_assert((TILE + 3) * 4 <= (int)sizeof(buf), "token staging fits");
+  const uint32_t P = 1u << ts.pbits;
+  const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
+  const uint64_t base = (uint64_t)tile * TILE;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  uint32_t glob[PER];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const uint32_t p = (uint32_t)tid * PER + k;
+    glob[k] = p < P ? offs[(size_t)p * ntiles + tile] : 0u;
+    loc[p] = 0u;
+  }
+  int32_t* s_tok = (int32_t*)buf;
+  stage_tokens<TILE, kPartThreads>(ts, nwin, base, s_tok);
+  __syncthreads();
+  K rem[IT];
+  uint32_t at[IT];  // partition << 16 | place in the tile's run; ~0: no window
+#pragma unroll
+  for (int r = 0; r < IT; ++r) {
+    const uint32_t j = (uint32_t)r * kPartThreads + tid;
+    uint32_t part;
+    const bool ok = split_window<NG>(s_tok + j, ts, &part, &rem[r]);
+    at[r] = ok && base + j < nwin ? (part << 16) | atomicAdd(&loc[part], 1u) : 0xFFFFFFFFu;
+  }
+  __syncthreads();
+  uint32_t c[PER], sum = 0;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    c[k] = loc[tid * PER + k];
+    sum += c[k];
+  }
+  uint32_t total;
+  uint32_t run = block_scan_excl<kPartThreads>(sum, s_wave, &total);
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    loc[tid * PER + k] = run;
+    dlt[tid * PER + k] = glob[k] - run;
+    run += c[k];
+  }
+  if (tid == 0) loc[PMAX] = total;
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < IT; ++r)
+    if (at[r] != 0xFFFFFFFFu) buf[loc[at[r] >> 16] + (at[r] & 0xFFFFu)] = rem[r];
+  __syncthreads();
+  constexpr uint32_t GR = 64 / LG;      // runs per wave and round
+  constexpr uint32_t LONG = 16 * LG;    // a run's part beyond this is left to the whole wave
+  for (uint32_t b0 = wave * GR; b0 < P; b0 += (kPartThreads / 64) * GR) {
+    const uint32_t bin = b0 + lane / LG;  // P is a multiple of GR
+    const uint32_t s = loc[bin], e = loc[bin + 1], d = dlt[bin];
+    const uint32_t e1 = min(e, s + LONG);
+    for (uint32_t q = s + lane % LG; q < e1; q += LG) out[(uint32_t)(q + d)] = buf[q];
+    uint64_t more = __builtin_amdgcn_ballot_w64(e > e1 && lane % LG == 0);
+    while (more) {
+      const int l = __builtin_ctzll(more);
+      more &= more - 1;
+      const uint32_t ls = (uint32_t)__builtin_amdgcn_readlane((int)e1, l);
+      const uint32_t le = (uint32_t)__builtin_amdgcn_readlane((int)e, l);
+      const uint32_t ld = (uint32_t)__builtin_amdgcn_readlane((int)d, l);
+      for (uint32_t q = ls + lane; q < le; q += 64) out[(uint32_t)(q + ld)] = buf[q];
+    }
+  }
+}
+
+// ---- 2. counting -------------------------------------------------------------------
+
+// Where everything lies, in one small device buffer (plan_words words).
+constexpr int kSelBins = 4096;
+constexpr uint32_t kMaxBuckets = 4096;
+struct Plan {
+  uint32_t* start;   // [P + 1]: partition p holds remainders [start[p], start[p + 1])
+  uint32_t* first;   // [P + 1]: its slices are [first[p], first[p + 1])
+  uint32_t* part;    // [slices]: partition of a slice
+  uint32_t* nslice;  // [slices]: distinct n-grams a slice's block found
+  uint32_t* nuniq;   // [P]: distinct n-grams of a partition
+  uint32_t* bins;    // [kSelBins]: n-grams with count min(i, kSelBins - 1)
+  uint32_t* tie;     // [512]: digit histogram of the tie selection
+  uint32_t* bcnt;    // [kMaxBuckets]: records per bucket
+  uint32_t* bcur;    // [kMaxBuckets]: records placed so far
+  uint32_t* bstart;  // [kMaxBuckets + 1]
+  uint64_t* state;   // [16], below
+};
+enum {
+  kStCstar, kStR, kStNeed, kStAbove, kStEqual, kStU,  // k_sel_small
+  kStPlaced,                                          // records gathered so far
+  kStTieHi, kStTieLo, kStTieNeed,                     // tie selection: key prefix, rank in it
+  kStFault,
+  kStWords = 16
+};
+size_t plan_words(uint32_t P, uint32_t slices) {
+  return 2 * ((size_t)P + 1) + 2 * (size_t)slices + P + kSelBins + 512 + 3 * (size_t)kMaxBuckets +
+         1 + 2 * kStWords + 2;
+}
+Plan plan_at(uint32_t* w, uint32_t P, uint32_t slices) {
+  Plan a;
+  a.state = (uint64_t*)w;
+  w += 2 * kStWords;
+  a.start = w;
+  a.first = a.start + P + 1;
+  a.part = a.first + P + 1;
+  a.nslice = a.part + slices;
+  a.nuniq = a.nslice + slices;
+  a.bins = a.nuniq + P;
+  a.tie = a.bins + kSelBins;
+  a.bcnt = a.tie + 512;
+  a.bcur = a.bcnt + kMaxBuckets;
+  a.bstart = a.bcur + kMaxBuckets;
+  return a;
+}
+
+// Partition starts from the scanned histogram (offs[P ntiles] is the number
+// of windows), slices of at most S remainders, and cleared counters.  One
+// block.
+__global__ __launch_bounds__(1024) void k_plan(Plan a, const uint32_t* offs, uint32_t ntiles,
+                                               uint32_t P, uint32_t S) {
+  __shared__ uint32_t s_wave[16];
+  const uint32_t tid = threadIdx.x;
+  for (uint32_t e = tid; e < kSelBins; e += 1024) a.bins[e] = 0u;
+  for (uint32_t e = tid; e < 512; e += 1024) a.tie[e] = 0u;
+  for (uint32_t e = tid; e < kMaxBuckets; e += 1024) a.bcnt[e] = a.bcur[e] = 0u;
+  if (tid < kStWords) a.state[tid] = 0ull;
+  constexpr int PER = kMaxParts / 1024;
+  uint32_t beg[PER], ns[PER], sum = 0;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const uint32_t p = tid * PER + k;
+    beg[k] = p < P ? offs[(size_t)p * ntiles] : 0u;
+    const uint32_t end = p < P ? offs[(size_t)(p + 1) * ntiles] : 0u;
+    ns[k] = (uint32_t)(((uint64_t)(end - beg[k]) + S - 1) / S);
+    sum += ns[k];
+  }
+  uint32_t total;
+  uint32_t run = block_scan_excl<1024>(sum, s_wave, &total);
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const uint32_t p = tid * PER + k;
+    if (p >= P) break;
+    a.start[p] = beg[k];
+    a.first[p] = run;
+    for (uint32_t j = 0; j < ns[k]; ++j) a.part[run + j] = p;
+    run += ns[k];
+  }
+  if (tid == 0) {
+    a.start[P] = offs[(size_t)P * ntiles];
+    a.first[P] = total;
+  }
+}
+
+// Hash of a remainder: its top bits pick the table entry, its low 16 bits
+// the part of the remainders that a retried table takes.
+__device__ __forceinline__ uint32_t rem_hash(uint32_t r) {
+  uint32_t h = r * 0x9E3779B1u;
+  h ^= h >> 15;
+  h *= 0x85EBCA77u;
+  return h ^ (h >> 13);
+}
+__device__ __forceinline__ uint32_t rem_hash(uint64_t r) {
+  uint32_t h = (uint32_t)r * 0x9E3779B1u;
+  h ^= ((uint32_t)(r >> 32) * 0x85EBCA77u);
+  h ^= h >> 15;
+  h *= 0xC2B2AE3Du;
+  return h ^ (h >> 13);
+}
+
+__device__ __forceinline__ uint32_t lane_of(uint32_t x, int l) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, l);
+}
+__device__ __forceinline__ uint64_t lane_of(uint64_t x, int l) {
+  return ((uint64_t)lane_of((uint32_t)(x >> 32), l) << 32) | lane_of((uint32_t)x, l);
+}
+
+// LDS table: 16384 entries of 32-bit remainders (128 KB) or 8192 of 64-bit
+// ones (96 KB).
+template <class K>
+constexpr uint32_t agg_slots() { return sizeof(K) == 4 ? 16384u : 8192u; }
+template <class K>
+struct Agg {
+  K key[agg_slots<K>()];
+  uint32_t cnt[agg_slots<K>()];
+  uint32_t over, out;
+};
+constexpr uint32_t kMaxProbe = 192;  // a longer probe gives the table up as full
+
+// The remainders that a (re)try takes: those whose selection string (the 16
+// low hash bits, then the remainder's own bits from the lowest) starts with
+// the `len` bits (vh, vr).  Different remainders have different strings, so
+// halving ends.
+struct Part2 {
+  int len;
+  uint32_t vh;
+  uint64_t vr;
+};
+template <class K>
+__device__ __forceinline__ bool taken(const Part2& s, uint32_t h, K r) {
+  if (s.len == 0) return true;
+  const int lh = min(s.len, 16), lr = s.len - lh;
+  return (h & ((1u << lh) - 1u)) == s.vh &&
+         (lr == 0 || ((uint64_t)r & ((1ull << lr) - 1ull)) == s.vr);
+}
+__device__ __forceinline__ void set_bit(Part2& s, int i, bool v) {
+  if (i < 16) s.vh = (s.vh & ~(1u << i)) | (v ? 1u << i : 0u);
+  else s.vr = (s.vr & ~(1ull << (i - 16))) | (v ? 1ull << (i - 16) : 0ull);
+}
+__device__ __forceinline__ bool get_bit(const Part2& s, int i) {
+  return i < 16 ? (s.vh >> i) & 1u : (s.vr >> (i - 16)) & 1ull;
+}
+
+// Adds w to the count of r, in the lanes with act.  ONE: w = 1 in every lane,
+// and the lanes that hold the first one's remainder add up first.
+template <class K, bool ONE>
+__device__ __forceinline__ void agg_add(Agg<K>& L, const Part2& sel, uint32_t mask, int hshift,
+                                        K r, uint32_t w, bool act) {
+  const uint32_t h = rem_hash(r);
+  act = act && taken(sel, h, r);
+  if (ONE) {
+    const uint64_t am = __builtin_amdgcn_ballot_w64(act);
+    if (!am) return;
+    const int f = __builtin_ctzll(am);
+    const uint64_t same = __builtin_amdgcn_ballot_w64(act && r == lane_of(r, f));
+    const int lane = threadIdx.x & 63;
+    if ((same >> lane) & 1ull) {
+      act = lane == f;
+      w = (uint32_t)__builtin_popcountll(same);
+    }
+  }
+  if (!act) return;
+  const K none = (K)~(K)0;
+  uint32_t s = (h >> hshift) & mask;
+  for (uint32_t n = 0; n < kMaxProbe; ++n) {
+    K k = __hip_atomic_load(&L.key[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (k == none) {
+      k = none;
+      if (__hip_atomic_compare_exchange_strong(&L.key[s], &k, r, __ATOMIC_RELAXED,
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))
+        k = r;
+    }
+    if (k == r) {
+      atomicAdd(&L.cnt[s], w);
+      return;
+    }
+    s = (s + 1) & mask;
+  }
+  L.over = 1u;
+}
+
+// Counts the remainders that feed(add) passes to add(r, w, act) (called by
+// whole waves; at most len in all), and writes the distinct ones with their
+// counts to okey / ocnt.  Returns their number (block-uniform).
+template <class K, bool ONE, class Feed>
+__device__ uint32_t agg_count(Agg<K>& L, uint32_t len, Feed feed, K* okey, uint32_t* ocnt,
+                              uint64_t* fault) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  uint32_t slots = agg_slots<K>();
+  int hshift = sizeof(K) == 4 ? 18 : 19;
+  static_assert(agg_slots<uint32_t>() == 1u << 14 && agg_slots<uint64_t>() == 1u << 13, "shift");
+  while (slots > 64 && slots / 2 >= 2 * (uint64_t)len) {
+    slots /= 2;
+    ++hshift;
+  }
+  const K none = (K)~(K)0;
+  const uint64_t lt = (1ull << lane) - 1ull;
+  if (tid == 0) L.out = 0u;
+  Part2 sel{0, 0u, 0ull};
+  for (;;) {
+    for (uint32_t e = tid; e < slots; e += 1024) {
+      L.key[e] = none;
+      L.cnt[e] = 0u;
+    }
+    if (tid == 0) L.over = 0u;
+    __syncthreads();
+    feed([&](K r, uint32_t w, bool act) { agg_add<K, ONE>(L, sel, slots - 1, hshift, r, w, act); },
+         [&] { return *(volatile uint32_t*)&L.over != 0u; });
+    __syncthreads();
+    const bool over = L.over != 0u;
+    if (over && sel.len < 16 + 63) {
+      __syncthreads();  // over is read before it is cleared
+      set_bit(sel, sel.len, false);
+      ++sel.len;
+      continue;
+    }
+    if (over && tid == 0) *fault = 1ull;  // not reached: such a part holds one remainder
+    for (uint32_t e = tid; e < slots; e += 1024) {
+      const uint32_t c = L.cnt[e];
+      const uint64_t m = __builtin_amdgcn_ballot_w64(c != 0u);
+      uint32_t o = 0;
+      if (m && lane == 0) o = atomicAdd(&L.out, (uint32_t)__builtin_popcountll(m));
+      o = __builtin_amdgcn_readfirstlane(o) + (uint32_t)__builtin_popcountll(m & lt);
+      if (c != 0u) {
+        okey[o] = L.key[e];
+        ocnt[o] = c;
+      }
+    }
+    __syncthreads();
+    while (sel.len > 0 && get_bit(sel, sel.len - 1)) set_bit(sel, --sel.len, false);
+    if (sel.len == 0) break;
+    set_bit(sel, sel.len - 1, true);
+  }
+  return L.out;
+}
+
+// One slice of a partition.
+template <class K>
+__global__ __launch_bounds__(1024) void k_count_slices(Plan a, const K* rem, uint32_t P, uint32_t S,
+                                                       K* ukey, uint32_t* ucnt) {
+  __shared__ Agg<K> L;
+  if (blockIdx.x >= a.first[P]) return;
+  const uint32_t p = a.part[blockIdx.x];
+  const uint32_t beg = a.start[p] + (blockIdx.x - a.first[p]) * S;
+  const uint32_t len = min(S, a.start[p + 1] - beg);
+  const K* src = rem + beg;
+  auto feed = [&](auto add, auto full) {
+    constexpr uint32_t U = 4;
+    for (uint32_t b = 0; b < len; b += 1024 * U) {
+      if (full()) break;
+      K r[U];
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        const uint32_t i = b + u * 1024 + threadIdx.x;
+        r[u] = src[i < len ? i : 0u];
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) add(r[u], 1u, b + u * 1024 + threadIdx.x < len);
+    }
+  };
+  const uint32_t n = agg_count<K, true>(L, len, feed, ukey + beg, ucnt + beg, a.state + kStFault);
+  if (threadIdx.x == 0) a.nslice[blockIdx.x] = n;
+}
+
+// The partial counts of a partition counted in several slices, added up
+// (one block per partition; the others only pass their number on).
+template <class K>
+__global__ __launch_bounds__(1024) void k_count_merge(Plan a, const K* ukey, const uint32_t* ucnt,
+                                                      uint32_t S, K* mkey, uint32_t* mcnt) {
+  __shared__ Agg<K> L;
+  const uint32_t p = blockIdx.x, f = a.first[p], ns = a.first[p + 1] - f, beg = a.start[p];
+  if (ns <= 1) {
+    if (threadIdx.x == 0) a.nuniq[p] = ns ? a.nslice[f] : 0u;
+    return;
+  }
+  const uint32_t len = a.start[p + 1] - beg;
+  auto feed = [&](auto add, auto full) {
+    for (uint32_t j = 0; j < ns; ++j) {
+      const uint32_t n = a.nslice[f + j], s = beg + j * S;
+      for (uint32_t b = 0; b < n; b += 1024) {
+        if (full()) return;
+        const uint32_t i = b + threadIdx.x;
+        const uint32_t q = s + (i < n ? i : 0u);
+        add(ukey[q], ucnt[q], i < n);
+      }
+    }
+  };
+  const uint32_t n = agg_count<K, false>(L, len, feed, mkey + beg, mcnt + beg, a.state + kStFault);
+  if (threadIdx.x == 0) a.nuniq[p] = n;
+}
+
+// The distinct n-grams: partition p's nuniq[p] keys and counts, in one of two
+// pairs of arrays.
+template <class K>
+struct Uniq {
+  Plan a;
+  const K *key, *mkey;          // counted in one slice; in several
+  const uint32_t *cnt, *mcnt;
+  uint32_t P;
+  __device__ __forceinline__ uint32_t at(uint32_t p, const K** k, const uint32_t** c) const {
+    const bool one = a.first[p + 1] - a.first[p] <= 1;
+    *k = (one ? key : mkey) + a.start[p];
+    *c = (one ? cnt : mcnt) + a.start[p];
+    return a.nuniq[p];
+  }
+};
+
+// ---- 3. selection -----------------------------------------------------------
+
+// Histogram of min(count, kSelBins - 1).  Most counts are small, so the
+// lanes holding the first lane's bin add their number with one atomic.
+template <class K>
+__global__ __launch_bounds__(1024) void k_sel_hist(Uniq<K> u) {
+  __shared__ uint32_t h[kSelBins];
+  for (uint32_t e = threadIdx.x; e < (uint32_t)kSelBins; e += 1024) h[e] = 0u;
+  __syncthreads();
+  const uint64_t lt = (1ull << (threadIdx.x & 63)) - 1ull;
+  for (uint32_t p = blockIdx.x; p < u.P; p += gridDim.x) {
+    const K* k;
+    const uint32_t* c;
+    const uint32_t n = u.at(p, &k, &c);
+    for (uint32_t b = 0; b < n; b += 1024) {
+      const uint32_t i = b + threadIdx.x;
+      const bool in = i < n;
+      const uint32_t bin = in ? min(c[i], (uint32_t)kSelBins - 1u) : 0u;
+      const uint32_t b0 = __builtin_amdgcn_readfirstlane(bin);
+      const uint64_t m = __builtin_amdgcn_ballot_w64(in && bin == b0);
+      if (in && bin != b0)
+        atomicAdd(&h[bin], 1u);
+      else if (in && (m & lt) == 0)
+        atomicAdd(&h[b0], (uint32_t)__builtin_popcountll(m));
+    }
+  }
+  __syncthreads();
+  for (uint32_t e = threadIdx.x; e < (uint32_t)kSelBins; e += 1024)
+    if (h[e]) atomicAdd(&u.a.bins[e], h[e]);
+}
+
+// One block: U distinct n-grams, R = min(want, U) ranks, c* = the R-th
+// largest count, the number above it, how many n-grams of count c* belong to
+// the R ranks and how many there are.  c* = kSelBins - 1 stands for every
+// count from there on.
+__global__ __launch_bounds__(1024) void k_sel_small(Plan a, uint64_t want) {
+  __shared__ uint32_t s_wave[16];
+  const uint32_t t = threadIdx.x;
+  uint32_t v[4], sum = 0;
+  for (int k = 0; k < 4; ++k) {
+    v[k] = a.bins[kSelBins - 1 - (4 * t + k)];  // bins in descending count order
+    sum += v[k];
+  }
+  uint32_t U;
+  uint32_t ex = block_scan_excl<1024>(sum, s_wave, &U);
+  const uint32_t R = (uint32_t)min(want, (uint64_t)U);
+  if (t == 0) {
+    a.state[kStU] = U;
+    a.state[kStR] = R;
+  }
+  for (int k = 0; k < 4; ++k) {
+    if (ex < R && R <= ex + v[k]) {
+      a.state[kStCstar] = kSelBins - 1 - (4 * t + k);
+      a.state[kStNeed] = R - ex;
+      a.state[kStTieNeed] = R - ex;
+      a.state[kStAbove] = ex;
+      a.state[kStEqual] = v[k];
+    }
+    ex += v[k];
+  }
+}
+
+// ---- 4. records ---------------------------------------------------------------
+
+// A record compares in rank order (smaller = earlier): 2^28 - count (28
+// bits) and the two oldest tokens, then the two newest.
+struct Rec1 {
+  uint64_t hi;
+};
+struct Rec2 {
+  uint64_t hi, lo;
+};
+__device__ __forceinline__ bool before(const Rec1& x, const Rec1& y) { return x.hi < y.hi; }
+__device__ __forceinline__ bool before(const Rec2& x, const Rec2& y) {
+  return x.hi < y.hi || (x.hi == y.hi && x.lo < y.lo);
+}
+template <int NG>
+using Rec = typename std::conditional<(NG <= 2), Rec1, Rec2>::type;
+template <class R>
+__device__ __forceinline__ R last_rec();
+template <>
+__device__ __forceinline__ Rec1 last_rec<Rec1>() { return Rec1{~0ull}; }
+template <>
+__device__ __forceinline__ Rec2 last_rec<Rec2>() { return Rec2{~0ull, ~0ull}; }
+
+__device__ __forceinline__ uint64_t key_hi(const uint32_t* x) { return ((uint64_t)x[0] << 18) | x[1]; }
+__device__ __forceinline__ uint64_t key_lo(const uint32_t* x) { return ((uint64_t)x[2] << 18) | x[3]; }
+__device__ __forceinline__ void make_rec(Rec1* r, uint32_t c, const uint32_t* x) {
+  r->hi = ((uint64_t)((1u << 28) - c) << 36) | key_hi(x);
+}
+__device__ __forceinline__ void make_rec(Rec2* r, uint32_t c, const uint32_t* x) {
+  r->hi = ((uint64_t)((1u << 28) - c) << 36) | key_hi(x);
+  r->lo = key_lo(x);
+}
+
+__device__ __forceinline__ void write_rank(const Rec1& r, int n, int32_t* t, int64_t* c) {
+  *c = (int64_t)((1u << 28) - (uint32_t)(r.hi >> 36));
+  t[0] = (int32_t)((r.hi >> 18) & kTok);
+  if (n == 2) t[1] = (int32_t)(r.hi & kTok);
+}
+__device__ __forceinline__ void write_rank(const Rec2& r, int n, int32_t* t, int64_t* c) {
+  *c = (int64_t)((1u << 28) - (uint32_t)(r.hi >> 36));
+  t[0] = (int32_t)((r.hi >> 18) & kTok);
+  t[1] = (int32_t)(r.hi & kTok);
+  t[2] = (int32_t)((r.lo >> 18) & kTok);
+  if (n == 4) t[3] = (int32_t)(r.lo & kTok);
+}
+
+// Tie selection, digit d (9 bits, from the oldest token's high bits) of the
+// tuples with count c* whose earlier digits are the ones decided.
+template <int NG>
+__global__ __launch_bounds__(1024) void k_tie_hist(Uniq<Rem<NG>> u, int pbits, int d) {
+  __shared__ uint32_t h[512];
+  if (threadIdx.x < 512) h[threadIdx.x] = 0u;
+  __syncthreads();
+  const uint32_t cstar = (uint32_t)u.a.state[kStCstar];
+  const uint64_t ph = u.a.state[kStTieHi], pl = u.a.state[kStTieLo];
+  const int sh = 27 - 9 * (d & 3);  // of the digit in its 36-bit half
+  for (uint32_t p = blockIdx.x; p < u.P; p += gridDim.x) {
+    const Rem<NG>* k;
+    const uint32_t* c;
+    const uint32_t n = u.at(p, &k, &c);
+    for (uint32_t i = threadIdx.x; i < n; i += 1024) {
+      if (c[i] != cstar) continue;
+      uint32_t x[4];
+      join_window<NG>(p, k[i], pbits, x);
+      const uint64_t hi = key_hi(x), lo = key_lo(x);
+      const bool in = d < 4 ? (hi >> (sh + 9)) == (ph >> (sh + 9))
+                            : hi == ph && (lo >> (sh + 9)) == (pl >> (sh + 9));
+      if (in) atomicAdd(&h[((d < 4 ? hi : lo) >> sh) & 511u], 1u);
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < 512 && h[threadIdx.x]) atomicAdd(&u.a.tie[threadIdx.x], h[threadIdx.x]);
+}
+
+// One block: the digit that holds the needed tuple; clears the histogram.
+__global__ __launch_bounds__(512) void k_tie_pick(Plan a, int d) {
+  __shared__ uint32_t s_wave[8];
+  const uint32_t t = threadIdx.x;
+  const uint64_t need = a.state[kStTieNeed];
+  const uint32_t v = a.tie[t];
+  uint32_t tot;
+  const uint64_t ex = block_scan_excl<512>(v, s_wave, &tot);
+  a.tie[t] = 0u;
+  if (ex < need && need <= ex + v) {
+    a.state[d < 4 ? kStTieHi : kStTieLo] |= (uint64_t)t << (27 - 9 * (d & 3));
+    a.state[kStTieNeed] = need - ex;
+  }
+}
+
+// Records of the n-grams with count above c*, and of those at c* (every one;
+// with `tie`, up to the selected tuple), in no particular order.  A block
+// counts its share first and takes its places with one atomic.
+template <int NG>
+__global__ __launch_bounds__(1024) void k_gather(Uniq<Rem<NG>> u, int pbits, uint32_t tie,
+                                                 Rec<NG>* out, uint32_t cap) {
+  __shared__ uint32_t s_n;
+  const uint32_t cstar = (uint32_t)u.a.state[kStCstar];
+  const uint64_t th = u.a.state[kStTieHi], tl = u.a.state[kStTieLo];
+  const int lane = threadIdx.x & 63;
+  const uint64_t lt = (1ull << lane) - 1ull;
+  auto walk = [&](auto use) {
+    for (uint32_t p = blockIdx.x; p < u.P; p += gridDim.x) {
+      const Rem<NG>* k;
+      const uint32_t* c;
+      const uint32_t n = u.at(p, &k, &c);
+      for (uint32_t b = 0; b < n; b += 1024) {
+        const uint32_t i = b + threadIdx.x;
+        const uint32_t ci = i < n ? c[i] : 0u;
+        bool keep = ci >= cstar && ci != 0u;
+        uint32_t x[4] = {0u, 0u, 0u, 0u};
+        if (keep && tie && ci == cstar) {
+          join_window<NG>(p, k[i], pbits, x);
+          const uint64_t hi = key_hi(x);
+          keep = hi < th || (hi == th && key_lo(x) <= tl);
+        }
+        use(p, k, i, ci, keep);
+      }
+    }
+  };
+  if (threadIdx.x == 0) s_n = 0u;
+  __syncthreads();
+  walk([&](uint32_t, const Rem<NG>*, uint32_t, uint32_t, bool keep) {
+    const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
+    if (m && lane == 0) atomicAdd(&s_n, (uint32_t)__builtin_popcountll(m));
+  });
+  __syncthreads();
+  if (threadIdx.x == 0)
+    s_n = (uint32_t)atomicAdd((unsigned long long*)(u.a.state + kStPlaced), (unsigned long long)s_n);
+  __syncthreads();
+  walk([&](uint32_t p, const Rem<NG>* k, uint32_t i, uint32_t ci, bool keep) {
+    const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
+    uint32_t o = 0;
+    if (m && lane == 0) o = atomicAdd(&s_n, (uint32_t)__builtin_popcountll(m));
+    o = __builtin_amdgcn_readfirstlane(o) + (uint32_t)__builtin_popcountll(m & lt);
+    if (keep && o < cap) {
+      uint32_t x[4];
+      join_window<NG>(p, k[i], pbits, x);
+      Rec<NG> r;
+      make_rec(&r, ci, x);
+      out[o] = r;
+    }
+  });
+}
+
+// ---- 5. ranking ------------------------------------------------------------------
+
+// Bucket sort: splitters from a sorted sample (4 records per bucket), each
+// record's bucket by binary search, then one LDS sort per bucket, which
+// writes the ranks asked for.  A bucket holds about kBucketMean records of at
+// most kBucketCap (eight times that): larger ones, which a sample of
+// distinct records practically never leaves, are ranked by counting.
+constexpr uint32_t kBucketMean = 1024;
+constexpr uint32_t kBucketCap = 8192;
+template <class R>
+constexpr uint32_t max_buckets() { return sizeof(R) == 8 ? 4096u : 2048u; }
+// Most records the bucket sort takes (2048 per bucket on average).
+template <class R>
+constexpr uint64_t bucket_sort_max() { return 2048ull * max_buckets<R>(); }
+
+// Bitonic sort of a[0, N2) in LDS, ascending; N2 a power of two.
+template <class R>
+__device__ void lds_sort(R* a, uint32_t N2) {
+  for (uint32_t size = 2; size <= N2; size <<= 1) {
+    for (uint32_t stride = size >> 1; stride > 0; stride >>= 1) {
+      __syncthreads();
+      for (uint32_t e = threadIdx.x; e < N2 / 2; e += 1024) {
+        const uint32_t i = 2 * e - (e & (stride - 1));
+        const uint32_t j = i + stride;
+        const R x = a[i], y = a[j];
+        if (before(y, x) == ((i & size) == 0)) {
+          a[i] = y;
+          a[j] = x;
+        }
+      }
+    }
+  }
+  __syncthreads();
+}
+
+// nb - 1 splitters (nb a power of two): every fourth of 4 nb sampled records.
+template <class R>
+__global__ __launch_bounds__(1024) void k_bk_sample(const R* rec, uint64_t K, uint32_t nb,
+                                                    R* split) {
+  __shared__ R s[4 * max_buckets<R>()];
+  const uint32_t ns = 4 * nb;
+  for (uint32_t e = threadIdx.x; e < ns; e += 1024) s[e] = rec[(uint64_t)e * K / ns];
+  lds_sort(s, ns);
+  for (uint32_t b = 1 + threadIdx.x; b < nb; b += 1024) split[b - 1] = s[4 * b];
+}
+
+constexpr uint32_t kBkTile = 4096;
+
+// Bucket of every record: the number of splitters at or before it.
+template <class R>
+__global__ __launch_bounds__(1024) void k_bk_hist(Plan a, const R* rec, uint64_t K, uint32_t nb,
+                                                  const R* split, uint16_t* bkt) {
+  __shared__ R s[max_buckets<R>()];
+  __shared__ uint32_t c[max_buckets<R>()];
+  for (uint32_t e = threadIdx.x; e < nb; e += 1024) {
+    s[e] = e + 1 < nb ? split[e] : last_rec<R>();
+    c[e] = 0u;
+  }
+  __syncthreads();
+#pragma unroll
+  for (uint32_t q = 0; q < kBkTile / 1024; ++q) {
+    const uint64_t i = (uint64_t)blockIdx.x * kBkTile + q * 1024 + threadIdx.x;
+    if (i < K) {
+      const R x = rec[i];
+      uint32_t lo = 0;
+      for (uint32_t h = nb >> 1; h; h >>= 1)
+        if (!before(x, s[lo + h - 1])) lo += h;
+      atomicAdd(&c[lo], 1u);
+      bkt[i] = (uint16_t)lo;
+    }
+  }
+  __syncthreads();
+  for (uint32_t e = threadIdx.x; e < nb; e += 1024)
+    if (c[e]) atomicAdd(&a.bcnt[e], c[e]);
+}
+
+template <class R>
+__global__ __launch_bounds__(1024) void k_bk_scatter(Plan a, const R* rec, uint64_t K, uint32_t nb,
+                                                     const uint16_t* bkt, R* out) {
+  __shared__ uint32_t c[max_buckets<R>()], base[max_buckets<R>()];
+  __shared__ uint32_t s_wave[16];
+  constexpr uint32_t PER = max_buckets<R>() / 1024;
+  const uint32_t tid = threadIdx.x;
+  uint32_t n[PER], sum = 0;
+#pragma unroll
+  for (uint32_t k = 0; k < PER; ++k) {
+    const uint32_t b = tid * PER + k;
+    n[k] = b < nb ? a.bcnt[b] : 0u;
+    sum += n[k];
+    c[b] = 0u;
+  }
+  uint32_t tot;
+  uint32_t run = block_scan_excl<1024>(sum, s_wave, &tot);
+#pragma unroll
+  for (uint32_t k = 0; k < PER; ++k) {
+    const uint32_t b = tid * PER + k;
+    base[b] = run;
+    if (blockIdx.x == 0 && b <= nb) a.bstart[b] = run;
+    run += n[k];
+  }
+  if (blockIdx.x == 0 && tid == 0) a.bstart[nb] = tot;
+  __syncthreads();
+  uint32_t at[kBkTile / 1024], b[kBkTile / 1024];
+#pragma unroll
+  for (uint32_t q = 0; q < kBkTile / 1024; ++q) {
+    const uint64_t i = (uint64_t)blockIdx.x * kBkTile + q * 1024 + tid;
+    b[q] = i < K ? bkt[i] : 0u;
+    at[q] = i < K ? atomicAdd(&c[b[q]], 1u) : 0u;
+  }
+  __syncthreads();
+  for (uint32_t e = tid; e < nb; e += 1024)
+    if (c[e]) base[e] += atomicAdd(&a.bcur[e], c[e]);
+  __syncthreads();
+#pragma unroll
+  for (uint32_t q = 0; q < kBkTile / 1024; ++q) {
+    const uint64_t i = (uint64_t)blockIdx.x * kBkTile + q * 1024 + tid;
+    if (i < K) out[base[b[q]] + at[q]] = rec[i];
+  }
+}
+
+// Sorts one bucket (whole = 0: the only one) and writes its ranks in
+// [skip, R).
+template <class R>
+__global__ __launch_bounds__(1024) void k_bk_sort(Plan a, const R* rec, uint32_t whole,
+                                                  uint64_t skip, uint64_t ranks, int n,
+                                                  int32_t* tuples, int64_t* counts) {
+  __shared__ R s[kBucketCap];
+  const uint32_t beg = whole ? 0u : a.bstart[blockIdx.x];
+  const uint32_t m = whole ? whole : a.bstart[blockIdx.x + 1] - beg;
+  if (m == 0 || beg >= ranks || (uint64_t)beg + m <= skip) return;
+  auto emit = [&](uint64_t rank, const R& r) {
+    if (rank >= skip && rank < ranks) write_rank(r, n, tuples + (rank - skip) * n, counts + (rank - skip));
+  };
+  if (m > kBucketCap) {
+    for (uint32_t e = threadIdx.x; e < m; e += 1024) {
+      const R x = rec[beg + e];
+      uint32_t r = 0;
+      for (uint32_t q = 0; q < m; ++q) r += before(rec[beg + q], x) ? 1u : 0u;
+      emit((uint64_t)beg + r, x);
+    }
+    return;
+  }
+  uint32_t N2 = 2;
+  while (N2 < m) N2 <<= 1;
+  for (uint32_t e = threadIdx.x; e < N2; e += 1024) s[e] = e < m ? rec[beg + e] : last_rec<R>();
+  lds_sort(s, N2);
+  for (uint32_t e = threadIdx.x; e < m; e += 1024) emit((uint64_t)beg + e, s[e]);
+}
+
+// Tiles of the radix sort: 512 threads (one per digit), 8 keys per thread
+// for keys alone (4096 keys: 52 KB of LDS, three tiles per CU) and 6 with a
+// payload.  The histogram of a tile is counted by 1024 threads.
+constexpr int kTileThreads = 512;
+constexpr int kTileWaves = kTileThreads / 64;
+constexpr int kHistThreads = 1024;
+template <class K, bool PAIRS, class V>
+constexpr int tile_items() { return (sizeof(K) + (PAIRS ? sizeof(V) : 0)) > 8 ? 6 : 8; }
+template <class K, bool PAIRS, class V>
+constexpr int tile_keys() { return kTileThreads * tile_items<K, PAIRS, V>(); }
+constexpr int kDigitBits = 9;
+constexpr uint32_t kBins = 1u << kDigitBits;
+static_assert(kBins <= (uint32_t)kTileThreads, "one scatter thread per digit");
+
+// ---- 6. long rankings: stable LSD radix sort (9-bit digits) -----------------
+//
+// Records beyond what the bucket sort holds (millions of ranks asked for).
 
 template <class K>
 __device__ __forceinline__ uint32_t digit_of(K k, int shift) {
   return (uint32_t)(k >> shift) & (kBins - 1u);
-}
-
-// Radix tile of this block.  Workgroups are dispatched round-robin over the
-// 8 XCDs (each with its own L2); giving every XCD a contiguous range of
-// tiles keeps the 32 tiles that share a 128-byte line of the digit-major
-// histogram matrix on one XCD, so each line is written and read through
-// one L2 instead of eight.  A bijection of [0, G) for any G.
-__device__ __forceinline__ uint32_t xcd_tile(uint32_t b, uint32_t G) {
-  const uint32_t q = G >> 3, r = G & 7u, x = b & 7u;
-  return x * q + min(x, r) + (b >> 3);
 }
 
 // Lanes of the wave whose digit equals this lane's (active lanes only).
@@ -341,29 +1080,19 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, bool active) {
 // digits (high bits of frequent tokens are mostly 0) would otherwise pile
 // same-address LDS atomics onto one bin; measured on MI355X this beats both
 // plain atomics and counting every group of equal digits once.
-template <class K, int TILE, int SRC>
-__global__ __launch_bounds__(kHistThreads) void k_rs_hist(const K* keys, TokSrc ts, uint64_t n,
-                                                          int shift, uint32_t* hist,
-                                                          uint32_t ntiles) {
+template <class K, int TILE>
+__global__ __launch_bounds__(kHistThreads) void k_rs_hist(const K* keys, uint64_t n, int shift,
+                                                          uint32_t* hist, uint32_t ntiles) {
   constexpr int ITEMS = TILE / kHistThreads;
-  constexpr bool kTok = SRC != kSrcKeys;
   __shared__ uint32_t h[kBins];
-  __shared__ int32_t s_tok[kTok ? TILE + 3 : 1];
   for (int e = threadIdx.x; e < (int)kBins; e += kHistThreads) h[e] = 0u;
   const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
   const uint64_t base = (uint64_t)tile * TILE;
-  if (kTok) {
-    stage_tokens<TILE, kHistThreads>(ts, n, base, s_tok);
-    __syncthreads();
-  }
   K kk[ITEMS];
 #pragma unroll
   for (int k = 0; k < ITEMS; ++k) {
     const uint64_t i = base + (uint64_t)k * kHistThreads + threadIdx.x;
-    if (kTok)
-      kk[k] = i < n ? key_at_lds<SRC, K>(s_tok, (uint32_t)(i - base), ts) : (K)0;
-    else
-      kk[k] = i < n ? keys[i] : (K)0;
+    kk[k] = i < n ? keys[i] : (K)0;
   }
   __syncthreads();
   const uint64_t lt = (1ull << (threadIdx.x & 63)) - 1ull;
@@ -390,9 +1119,9 @@ __global__ __launch_bounds__(kHistThreads) void k_rs_hist(const K* keys, TokSrc 
 // plus the matching lanes below it; the first lane of each digit group
 // advances the count.  Tile positions follow (digit, wave, rank), i.e. the
 // stable order; the tile is reordered in LDS and written in digit runs.
-template <class K, class V, bool PAIRS, int ITEMS, int SRC>
+template <class K, class V, bool PAIRS, int ITEMS>
 __global__ __launch_bounds__(kTileThreads) void k_rs_scatter(const K* keys, const V* vals,
-                                                             TokSrc ts, uint64_t n, int shift,
+                                                             uint64_t n, int shift,
                                                              const uint32_t* offs,
                                                              uint32_t ntiles, K* keys_out,
                                                              V* vals_out) {
@@ -408,29 +1137,14 @@ __global__ __launch_bounds__(kTileThreads) void k_rs_scatter(const K* keys, cons
   const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
   const uint64_t base = (uint64_t)tile * TILE + (uint64_t)wave * (64 * ITEMS);
   const uint64_t lt = (1ull << lane) - 1ull;
-  // Token-sourced keys: the tile's tokens are staged in the reorder buffer,
-  // which is free until the keys are placed (two barriers later).
-  constexpr bool kTok = SRC != kSrcKeys;
-  static_assert(!kTok || (TILE + 3) * 4 <= TILE * (int)sizeof(K), "token staging fits");
-  int32_t* s_tok = (int32_t*)s_keys;
-  if (kTok) {
-    stage_tokens<TILE, kTileThreads>(ts, n, (uint64_t)tile * TILE, s_tok);
-    __syncthreads();
-  }
   K kk[ITEMS];
   V vv[PAIRS ? ITEMS : 1];
   uint32_t rank[ITEMS];
 #pragma unroll
   for (int r = 0; r < ITEMS; ++r) {
     const uint64_t i = base + (uint64_t)r * 64 + lane;
-    const uint32_t j = (uint32_t)(i - (uint64_t)tile * TILE);
-    if (kTok) {
-      kk[r] = i < n ? key_at_lds<SRC, K>(s_tok, j, ts) : (K)0;
-      if (PAIRS) vv[PAIRS ? r : 0] = i < n ? (V)val4_at_lds(s_tok, j, ts) : (V)0;
-    } else {
-      kk[r] = i < n ? keys[i] : (K)0;
-      if (PAIRS) vv[PAIRS ? r : 0] = i < n ? vals[i] : (V)0;
-    }
+    kk[r] = i < n ? keys[i] : (K)0;
+    if (PAIRS) vv[PAIRS ? r : 0] = i < n ? vals[i] : (V)0;
   }
   __syncthreads();
 #pragma unroll
@@ -483,375 +1197,30 @@ __global__ __launch_bounds__(kTileThreads) void k_rs_scatter(const K* keys, cons
     if (PAIRS) vals_out[dst] = s_vals[PAIRS ? p : 0];
   }
 }
-
-// ---- 3. run-length count ----------------------------------------------------
-
-// Runs of equal keys in the sorted valid keys (hi: the high key word of
-// 4-grams, or null), in two passes shaped like the scan: the number of run
-// starts per block, then (after the scan of those counts) each start's key
-// and position at its rank.  A start is a key that differs from the one
-// before it.  Wave w of a block covers kScanItems rounds of 64 keys.
-
-// Run starts among the kScanItems rounds of 64 keys of this wave from base:
-// the keys (and high words) are loaded first, at clamped indices, so that
-// all loads are in flight at once; each key's predecessor comes from the
-// lane below (lane 0: lane 63 of the round before, or one load for the
-// wave's first key); then one ballot per round.  cur keeps the keys (and
-// hcur the high words).
-__device__ __forceinline__ uint64_t from_lane_below(uint64_t x, uint64_t carry) {
-  const int lane = threadIdx.x & 63;
-  const uint32_t lo = (uint32_t)__shfl_up((int)(uint32_t)x, 1, 64);
-  const uint32_t hi = (uint32_t)__shfl_up((int)(uint32_t)(x >> 32), 1, 64);
-  return lane == 0 ? carry : ((uint64_t)hi << 32) | lo;
-}
-
-__device__ __forceinline__ uint64_t lane63(uint64_t x) {
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, 63);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), 63);
-  return ((uint64_t)hi << 32) | lo;
-}
-
-template <bool WIDE>
-__device__ __forceinline__ void run_starts(const uint64_t* keys, const uint32_t* hi, uint64_t base,
-                                           uint64_t n, uint64_t (&m)[kScanItems],
-                                           uint64_t (&cur)[kScanItems],
-                                           uint32_t (&hcur)[WIDE ? kScanItems : 1]) {
-  const int lane = threadIdx.x & 63;
-  const uint64_t i0 = base > 0 ? (base - 1 < n ? base - 1 : n - 1) : 0;
-  const uint64_t first = keys[i0];
-  const uint32_t hfirst = WIDE ? hi[i0] : 0u;
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    const uint64_t i = base + (uint64_t)k * 64 + lane;
-    const uint64_t ic = i < n ? i : n - 1;
-    cur[k] = keys[ic];
-    if (WIDE) hcur[WIDE ? k : 0] = hi[ic];
-  }
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    const uint64_t i = base + (uint64_t)k * 64 + lane;
-    const uint64_t prv = from_lane_below(cur[k], k == 0 ? first : lane63(cur[k > 0 ? k - 1 : 0]));
-    bool differs = cur[k] != prv;
-    if (WIDE) {
-      const uint32_t hc = hcur[WIDE ? k : 0];
-      const uint32_t hcarry =
-          k == 0 ? hfirst
-                 : (uint32_t)__builtin_amdgcn_readlane((int)hcur[WIDE ? (k > 0 ? k - 1 : 0) : 0], 63);
-      // Shuffled in every lane before the select: a lane that reads an
-      // inactive one gets 0.
-      const uint32_t below = (uint32_t)__shfl_up((int)hc, 1, 64);
-      const uint32_t hp = lane == 0 ? hcarry : below;
-      differs = differs || hc != hp;
-    }
-    m[k] = __builtin_amdgcn_ballot_w64(i < n && (i == 0 || differs));
-  }
-}
-
-template <bool WIDE>
-__global__ __launch_bounds__(kScanThreads) void k_runs_reduce(const uint64_t* keys,
-                                                              const uint32_t* hi, uint64_t n,
-                                                              uint32_t* part) {
-  __shared__ uint32_t s_tot[kScanThreads / 64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint64_t base = (uint64_t)blockIdx.x * kScanBlock + (uint64_t)wave * (64 * kScanItems);
-  uint64_t m[kScanItems], cur[kScanItems];
-  uint32_t hcur[WIDE ? kScanItems : 1];
-  run_starts<WIDE>(keys, hi, base, n, m, cur, hcur);
-  uint32_t c = 0;
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) c += (uint32_t)__builtin_popcountll(m[k]);
-  if (lane == 0) s_tot[wave] = c;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t t = 0;
-    for (int w = 0; w < kScanThreads / 64; ++w) t += s_tot[w];
-    part[blockIdx.x] = t;
-  }
-}
-
-template <bool WIDE>
-__global__ __launch_bounds__(kScanThreads) void k_runs_write(const uint64_t* keys,
-                                                             const uint32_t* hi, uint64_t n,
-                                                             const uint32_t* part, uint64_t* ukey,
-                                                             uint32_t* uhi, uint32_t* ustart) {
-  __shared__ uint32_t s_tot[kScanThreads / 64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint64_t base = (uint64_t)blockIdx.x * kScanBlock + (uint64_t)wave * (64 * kScanItems);
-  uint64_t m[kScanItems], cur[kScanItems];
-  uint32_t hcur[WIDE ? kScanItems : 1];
-  run_starts<WIDE>(keys, hi, base, n, m, cur, hcur);
-  uint32_t c = 0;
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) c += (uint32_t)__builtin_popcountll(m[k]);
-  if (lane == 0) s_tot[wave] = c;
-  __syncthreads();
-  uint32_t r = part[blockIdx.x];
-  for (int w = 0; w < wave; ++w) r += s_tot[w];
-  const uint64_t lt = (1ull << lane) - 1ull;
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    const uint64_t i = base + (uint64_t)k * 64 + lane;
-    if ((m[k] >> lane) & 1ull) {
-      const uint32_t idx = r + (uint32_t)__builtin_popcountll(m[k] & lt);
-      ukey[idx] = cur[k];
-      if (WIDE) uhi[idx] = hcur[WIDE ? k : 0];
-      ustart[idx] = (uint32_t)i;
-    }
-    r += (uint32_t)__builtin_popcountll(m[k]);
-  }
-}
-
-// Run lengths, and the histogram of min(count, kSelBins - 1) for the
-// selection (per-block LDS bins added to the global ones).
-constexpr int kSelBins = 4096;
-
-__global__ __launch_bounds__(1024) void k_run_counts(const uint32_t* ustart, uint32_t u,
-                                                     uint32_t n, uint32_t* ucount,
-                                                     uint32_t* bins) {
-  __shared__ uint32_t h[kSelBins];
-  for (int e = threadIdx.x; e < kSelBins; e += 1024) h[e] = 0u;
-  __syncthreads();
-  const uint32_t base = blockIdx.x * (1024u * 16u);
-  for (int k = 0; k < 16; ++k) {
-    const uint32_t i = base + (uint32_t)k * 1024u + threadIdx.x;
-    const bool in = i < u;
-    uint32_t bin = 0;
-    if (in) {
-      const uint32_t c = (i + 1 < u ? ustart[i + 1] : n) - ustart[i];
-      ucount[i] = c;
-      bin = c < (uint32_t)kSelBins ? c : (uint32_t)kSelBins - 1u;
-    }
-    // Most runs are short, so most lanes share a bin: the lanes holding the
-    // first lane's bin add their number with one atomic (one atomic per
-    // lane put 64-way same-address atomics on the few small-count bins).
-    if (__builtin_amdgcn_ballot_w64(in)) {
-      const uint32_t b0 = __builtin_amdgcn_readfirstlane(bin);
-      const uint64_t m = __builtin_amdgcn_ballot_w64(in && bin == b0);
-      if (in && bin != b0)
-        atomicAdd(&h[bin], 1u);
-      else if (in && (m & ((1ull << (threadIdx.x & 63)) - 1ull)) == 0)
-        atomicAdd(&h[b0], (uint32_t)__builtin_popcountll(m));
-    }
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < kSelBins; e += 1024)
-    if (h[e]) atomicAdd(&bins[e], h[e]);
-}
-
-// ---- 4. selection -----------------------------------------------------------
-
-// The selection state: {prefix, mask, need, above, done}.  After the
-// selection, prefix = c* (the R-th largest count), need = how many runs of
-// count c* belong to ranks [0, R), above = the runs with larger counts.
-
-// From the histogram of min(count, kSelBins - 1) (one block, 1024 threads,
-// 4 bins each from the top): if c* < kSelBins - 1 the selection is done;
-// otherwise the radix passes below find it.
-__global__ __launch_bounds__(1024) void k_sel_small(const uint32_t* bins, uint32_t* state) {
-  __shared__ uint32_t s_wave[16];
-  const uint32_t t = threadIdx.x;
-  const uint32_t need = state[2];
-  uint32_t v[4], sum = 0;
-  for (int k = 0; k < 4; ++k) {
-    v[k] = bins[kSelBins - 1 - (4 * t + k)];  // bins in descending count order
-    sum += v[k];
-  }
-  uint32_t tot;
-  uint32_t ex = block_scan_excl<1024>(sum, s_wave, &tot);
-  for (int k = 0; k < 4; ++k) {
-    const uint32_t c = kSelBins - 1 - (4 * t + k);
-    if (ex < need && need <= ex + v[k] && c < (uint32_t)kSelBins - 1) {
-      state[0] = c;
-      state[1] = 0xFFFFFFFFu;
-      state[2] = need - ex;
-      state[3] = ex;
-      state[4] = 1u;
-    }
-    ex += v[k];
-  }
-}
-
-// Histogram of digit `shift` of the counts whose higher digits equal
-// `prefix` (under `mask`): one pass of a radix select on a 32-bit value.
-__global__ __launch_bounds__(256) void k_sel_hist(const uint32_t* cnt, uint32_t u,
-                                                  const uint32_t* state, int shift,
-                                                  uint32_t* hist) {
-  __shared__ uint32_t h[256];
-  if (state[4]) return;  // done from the small-count histogram
-  h[threadIdx.x] = 0u;
-  __syncthreads();
-  const uint32_t prefix = state[0], mask = state[1];
-  for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < u; i += gridDim.x * 256) {
-    const uint32_t c = cnt[i];
-    if ((c & mask) == prefix) atomicAdd(&h[(c >> shift) & 255u], 1u);
-  }
-  __syncthreads();
-  if (h[threadIdx.x]) atomicAdd(&hist[threadIdx.x], h[threadIdx.x]);
-}
-
-// One block: pick the digit bin holding the need-th largest, update the
-// state {prefix, mask, need, above} and clear the histogram.
-__global__ __launch_bounds__(256) void k_sel_pick(uint32_t* hist, uint32_t* state, int shift) {
-  __shared__ uint32_t s_wave[4];
-  const uint32_t t = threadIdx.x;
-  // Every thread reads the state before the scan's barriers, so the one
-  // update below cannot be seen by a late reader.
-  if (state[4]) return;
-  const uint32_t need = state[2];
-  const uint32_t v = hist[255 - t];  // thread t looks at bin 255 - t
-  uint32_t tot;
-  const uint32_t ex = block_scan_excl<256>(v, s_wave, &tot);
-  if (ex < need && need <= ex + v) {
-    state[0] |= (255u - t) << shift;
-    state[1] |= 255u << shift;
-    state[2] = need - ex;
-    state[3] += ex;
-  }
-  hist[255 - t] = 0u;
-}
-
-// keep[i]: count > c*, or count == c* and among the first `need` such runs.
-// The runs that make ranks [0, R): with c* = state[0] and need = state[2],
-// run i is kept when its count exceeds c*, or equals c* and fewer than
-// `need` runs of count c* come before it.  Kept runs keep their order
-// (rkey = ~count, rval = the run index): the stable sort that ranks them
-// then leaves equal counts in tuple order.  Two launches over the counts:
-// per-block numbers above and at c*, then each block places its kept runs.
-
-// Per block of kScanBlock runs: how many counts exceed c* and how many
-// equal it.
-__global__ __launch_bounds__(kScanThreads) void k_sel_count(const uint32_t* cnt, uint32_t u,
-                                                            const uint32_t* state,
-                                                            uint32_t* part_gt, uint32_t* part_eq) {
-  __shared__ uint32_t s_gt[kScanThreads / 64], s_eq[kScanThreads / 64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint32_t cstar = state[0];  // >= 1: the R-th largest count
-  const uint64_t base = (uint64_t)blockIdx.x * kScanBlock + (uint64_t)wave * (64 * kScanItems);
-  uint32_t c[kScanItems];
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    const uint64_t i = base + (uint64_t)k * 64 + lane;
-    c[k] = i < u ? cnt[i] : 0u;  // 0: no run
-  }
-  uint32_t g = 0, e = 0;
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    g += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(c[k] > cstar));
-    e += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(c[k] == cstar));
-  }
-  if (lane == 0) {
-    s_gt[wave] = g;
-    s_eq[wave] = e;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t tg = 0, te = 0;
-    for (int w = 0; w < kScanThreads / 64; ++w) {
-      tg += s_gt[w];
-      te += s_eq[w];
-    }
-    part_gt[blockIdx.x] = tg;
-    part_eq[blockIdx.x] = te;
-  }
-}
-
-// Places the block's kept runs.  The runs above c* before the block, and
-// the kept ones at c* (the first `need` of them, in order), are added up
-// from the per-block numbers of the earlier blocks (at most kScanItems per
-// thread, from L2); within the block each wave takes its contiguous
-// kScanItems x 64 runs, ranks the ones at c* and then the kept ones with
-// ballots, and one exchange of wave totals places the waves.  Positions at
-// or past R (none when the selection state is consistent) are not written.
-__global__ __launch_bounds__(kScanThreads) void k_sel_place(const uint32_t* cnt, uint32_t u,
-                                                            const uint32_t* state,
-                                                            const uint32_t* part_gt,
-                                                            const uint32_t* part_eq, uint32_t R,
-                                                            uint32_t* rkey, uint64_t* rval) {
-  __shared__ uint64_t s_sum[kScanThreads / 64];
-  __shared__ uint32_t s_eq[kScanThreads / 64], s_keep[kScanThreads / 64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint32_t cstar = state[0], need = state[2];
-  const uint64_t base = (uint64_t)blockIdx.x * kScanBlock + (uint64_t)wave * (64 * kScanItems);
-  uint32_t c[kScanItems];
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    const uint64_t i = base + (uint64_t)k * 64 + lane;
-    c[k] = i < u ? cnt[i] : 0u;
-  }
-  // Earlier blocks: above c* in the high word, at c* in the low word (each
-  // total is below 2^32).
-  uint64_t b = 0;
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    const uint32_t j = (uint32_t)k * kScanThreads + threadIdx.x;
-    if (j < blockIdx.x) b += ((uint64_t)part_gt[j] << 32) | part_eq[j];
-  }
-  for (int d = 32; d >= 1; d >>= 1) b += __shfl_xor(b, d, 64);
-  if (lane == 0) s_sum[wave] = b;
-  const uint64_t lt = (1ull << lane) - 1ull;
-  uint64_t em[kScanItems];
-  uint32_t e = 0;
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    em[k] = __builtin_amdgcn_ballot_w64(c[k] == cstar);
-    e += (uint32_t)__builtin_popcountll(em[k]);
-  }
-  if (lane == 0) s_eq[wave] = e;
-  __syncthreads();
-  uint64_t before = 0;
-  for (int w = 0; w < kScanThreads / 64; ++w) before += s_sum[w];
-  const uint32_t gt_before = (uint32_t)(before >> 32), eq_before = (uint32_t)before;
-  uint32_t erun = eq_before;
-  for (int w = 0; w < wave; ++w) erun += s_eq[w];
-  uint64_t km[kScanItems];
-  uint32_t kc = 0;
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    const uint32_t er = erun + (uint32_t)__builtin_popcountll(em[k] & lt);
-    const bool keep = c[k] > cstar || (((em[k] >> lane) & 1ull) && er < need);
-    km[k] = __builtin_amdgcn_ballot_w64(keep);
-    kc += (uint32_t)__builtin_popcountll(km[k]);
-    erun += (uint32_t)__builtin_popcountll(em[k]);
-  }
-  if (lane == 0) s_keep[wave] = kc;
-  __syncthreads();
-  uint32_t krun = gt_before + min(need, eq_before);
-  for (int w = 0; w < wave; ++w) krun += s_keep[w];
-#pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    if ((km[k] >> lane) & 1ull) {
-      const uint32_t pos = krun + (uint32_t)__builtin_popcountll(km[k] & lt);
-      if (pos < R) {
-        rkey[pos] = ~c[k];  // ascending ~count = descending count
-        rval[pos] = base + (uint64_t)k * 64 + lane;
-      }
-    }
-    krun += (uint32_t)__builtin_popcountll(km[k]);
-  }
-}
-
-// ---- 6. output ----------------------------------------------------------------
-
-__global__ __launch_bounds__(256) void k_unpack(const uint32_t* rkey, const uint64_t* rval,
-                                                const uint64_t* ukey, const uint32_t* uhi,
-                                                uint64_t skip, uint64_t m, int n,
-                                                int32_t* tuples, int64_t* counts) {
+// Words of records that the two radix key arrays hold, and back.
+__global__ __launch_bounds__(256) void k_split_rec2(const Rec2* rec, uint64_t K, uint64_t* hi,
+                                                    uint64_t* lo) {
   const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < m) {
-    const uint64_t run = rval[skip + i];
-    const uint64_t k = ukey[run];
-    const int nlo = uhi ? 3 : n;  // tokens held in the low word
-    int32_t* t = tuples + i * n;
-    if (uhi) t[0] = (int32_t)uhi[run];
-    for (int j = 0; j < nlo; ++j)
-      t[n - nlo + j] = (int32_t)((k >> (18 * (nlo - 1 - j))) & 0x3FFFFu);
-    counts[i] = (int64_t)(uint32_t)~rkey[skip + i];
+  if (i < K) {
+    hi[i] = rec[i].hi;
+    lo[i] = rec[i].lo;
   }
+}
+
+__global__ __launch_bounds__(256) void k_unpack(const uint64_t* hi, const uint64_t* lo,
+                                                uint64_t skip, uint64_t m, int n, int32_t* tuples,
+                                                int64_t* counts) {
+  const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= m) return;
+  if (lo)
+    write_rank(Rec2{hi[skip + i], lo[skip + i]}, n, tuples + i * n, counts + i);
+  else
+    write_rank(Rec1{hi[skip + i]}, n, tuples + i * n, counts + i);
 }
 
 uint32_t blocks_for(uint64_t n, uint64_t per) { return (uint32_t)((n + per - 1) / per); }
 
-// Exclusive scan of n uint32 values (in may equal out); total to *total (device).
+// Exclusive scan of n uint32 values (in may equal out).
 hipError_t scan_u32(const uint32_t* in, uint32_t* out, uint64_t n, uint32_t* part,
                     hipStream_t s) {
   const uint32_t nb = blocks_for(n, kScanBlock);
@@ -862,37 +1231,22 @@ hipError_t scan_u32(const uint32_t* in, uint32_t* out, uint64_t n, uint32_t* par
   return hipGetLastError();
 }
 
-template <class K, class V, bool PAIRS, int SRC>
-hipError_t radix_pass(K* keys, K* keys_alt, V* vals, V* vals_alt, const TokSrc& ts,
-                      uint64_t n, int shift, uint32_t ntiles, uint32_t* hist, uint32_t* part,
-                      hipStream_t s) {
-  constexpr int ITEMS = tile_items<K, PAIRS, V>();
-  hipLaunchKernelGGL((k_rs_hist<K, tile_keys<K, PAIRS, V>(), SRC>), dim3(ntiles), dim3(kHistThreads),
-                     0, s, keys, ts, n, shift, hist, ntiles);
-  hipError_t e = scan_u32(hist, hist, (uint64_t)kBins * ntiles, part, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_rs_scatter<K, V, PAIRS, ITEMS, SRC>), dim3(ntiles), dim3(kTileThreads), 0, s,
-                     keys, vals, ts, n, shift, hist, ntiles, keys_alt, vals_alt);
-  return hipGetLastError();
-}
-
-// Stable LSD sort of n keys (and payloads) by their low `bits` bits; the
-// first pass reads its keys (and payloads) from SRC.  hist holds
-// kBins x ceil(n / kMinTile) entries.
-template <class K, bool PAIRS, int SRC = kSrcKeys, class V = uint64_t>
-hipError_t radix_sort(K*& keys, K*& keys_alt, V*& vals, V*& vals_alt, uint64_t n,
-                      int bits, uint32_t* hist, uint32_t* part, hipStream_t s,
-                      const TokSrc& ts = TokSrc{nullptr, 0, 0, 0, 0}) {
-  const uint32_t ntiles = blocks_for(n, tile_keys<K, PAIRS, V>());
-  if (ntiles == 0) return hipSuccess;
+// Stable LSD sort of n keys (and payloads) by their low `bits` bits.  hist
+// holds kBins x ceil(n / tile) entries.
+template <bool PAIRS>
+hipError_t radix_sort(uint64_t*& keys, uint64_t*& keys_alt, uint64_t*& vals, uint64_t*& vals_alt,
+                      uint64_t n, int bits, uint32_t* hist, uint32_t* part, hipStream_t s) {
+  using K = uint64_t;
+  constexpr int ITEMS = tile_items<K, PAIRS, K>();
+  constexpr int TILE = tile_keys<K, PAIRS, K>();
+  const uint32_t ntiles = blocks_for(n, TILE);
   for (int shift = 0; shift < bits; shift += kDigitBits) {
-    const hipError_t e =
-        shift == 0
-            ? radix_pass<K, V, PAIRS, SRC>(keys, keys_alt, vals, vals_alt, ts, n, shift, ntiles,
-                                        hist, part, s)
-            : radix_pass<K, V, PAIRS, kSrcKeys>(keys, keys_alt, vals, vals_alt, ts, n, shift,
-                                             ntiles, hist, part, s);
+    hipLaunchKernelGGL((k_rs_hist<K, TILE>), dim3(ntiles), dim3(kHistThreads), 0, s, keys, n, shift,
+                       hist, ntiles);
+    const hipError_t e = scan_u32(hist, hist, (uint64_t)kBins * ntiles, part, s);
     if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_rs_scatter<K, K, PAIRS, ITEMS>), dim3(ntiles), dim3(kTileThreads), 0, s,
+                       keys, vals, n, shift, hist, ntiles, keys_alt, vals_alt);
     std::swap(keys, keys_alt);
     if (PAIRS) std::swap(vals, vals_alt);
   }
@@ -974,13 +1328,143 @@ struct Scratch {
     hipError_t e_ = (call);                                                          \
     if (e_ != hipSuccess) return fail(TFE_ERR_HIP, "%s: %s", what, hipGetErrorString(e_)); \
   } while (0)
+// Partitions for nwin windows: enough that a partition's distinct n-grams
+// fit the LDS table (about 6000 of 8192 64-bit entries even when every
+// window is distinct; for n <= 2, where most windows repeat, 32768 windows
+// against 16384 entries), within what the scatter's LDS counters allow.
+int part_bits(uint64_t nwin, int n) {
+  const uint64_t mean = n <= 2 ? 32768 : 6000;
+  int b = kMinPartBits;
+  while (b < kMaxPartBits && (nwin >> b) > mean) ++b;
+  return b;
+}
+
+template <int NG>
+tfe_status ngram_top_n(const int32_t* tokens, uint64_t nwin, int32_t vocab, uint64_t skip,
+                       uint64_t top, int32_t* out_tuples, int64_t* out_counts, int64_t* written,
+                       hipStream_t s) {
+  using K = Rem<NG>;
+  using R = Rec<NG>;
+  Scratch sc(s);
+  const TokSrc ts{tokens, NG, vocab, part_bits(nwin, NG)};
+  const uint32_t P = 1u << ts.pbits;
+  const uint32_t ntiles = blocks_for(nwin, part_tile<NG>());
+  const uint64_t nhist = (uint64_t)P * ntiles;
+  // Slices of twice the mean partition, so that only heavily repeated
+  // n-grams make a partition span several.
+  const uint32_t S = (uint32_t)std::max<uint64_t>(16384, 2 * (nwin / P + 1));
+  const uint32_t slices = P + (uint32_t)(nwin / S) + 1;
+  uint32_t* hist = sc.get<uint32_t>(nhist + 1);
+  uint32_t* part = sc.get<uint32_t>(kScanBlock);
+  uint32_t* words = sc.get<uint32_t>(plan_words(P, slices));
+  K* rem = sc.get<K>(nwin);
+  K* ukey = sc.get<K>(nwin);
+  uint32_t* ucnt = sc.get<uint32_t>(nwin);
+  uint32_t* mcnt = sc.get<uint32_t>(nwin);
+  if (!hist || !part || !words || !rem || !ukey || !ucnt || !mcnt)
+    return fail(TFE_ERR_OOM, "n-gram scratch for %llu windows", (unsigned long long)nwin);
+  const Plan a = plan_at(words, P, slices);
+  // 1. Remainders grouped by partition.
+  BUILD_HIP(hipMemsetAsync(hist + nhist, 0, sizeof(uint32_t), s), "memset");
+  if (P <= 2048)
+    hipLaunchKernelGGL((k_part_hist<NG, 2048>), dim3(ntiles), dim3(kPartThreads), 0, s, ts, nwin,
+                       hist, ntiles);
+  else
+    hipLaunchKernelGGL((k_part_hist<NG, 4096>), dim3(ntiles), dim3(kPartThreads), 0, s, ts, nwin,
+                       hist, ntiles);
+  BUILD_HIP(scan_u32(hist, hist, nhist + 1, part, s), "partition scan");
+  hipLaunchKernelGGL(k_plan, dim3(1), dim3(1024), 0, s, a, hist, ntiles, P, S);
+  if (P <= 2048)
+    hipLaunchKernelGGL((k_part_scatter<NG, 2048>), dim3(ntiles), dim3(kPartThreads), 0, s, ts, nwin,
+                       hist, ntiles, rem);
+  else
+    hipLaunchKernelGGL((k_part_scatter<NG, 4096>), dim3(ntiles), dim3(kPartThreads), 0, s, ts, nwin,
+                       hist, ntiles, rem);
+  BUILD_HIP(hipGetLastError(), "partition launches");
+  // 2. Counts.  (A merged partition's n-grams take the place of its
+  // remainders.)
+  hipLaunchKernelGGL(k_count_slices<K>, dim3(slices), dim3(1024), 0, s, a, rem, P, S, ukey, ucnt);
+  hipLaunchKernelGGL(k_count_merge<K>, dim3(P), dim3(1024), 0, s, a, ukey, ucnt, S, rem, mcnt);
+  // 3. Selection.
+  const Uniq<K> u{a, ukey, rem, ucnt, mcnt, P};
+  const uint32_t walkers = std::min<uint32_t>(P, 512);
+  hipLaunchKernelGGL(k_sel_hist<K>, dim3(walkers), dim3(1024), 0, s, u);
+  hipLaunchKernelGGL(k_sel_small, dim3(1), dim3(1024), 0, s, a, skip + top);
+  BUILD_HIP(hipGetLastError(), "count launches");
+  uint64_t st[kStWords];
+  BUILD_HIP(hipMemcpyAsync(st, a.state, sizeof st, hipMemcpyDeviceToHost, s), "copy");
+  BUILD_HIP(hipStreamSynchronize(s), "sync");
+  if (st[kStFault]) return fail(TFE_ERR_HIP, "n-gram count table");
+  const uint64_t ranks = st[kStR];
+  if (ranks <= skip) return TFE_OK;
+  // 4. Records.  Many more ties at c* than needed: select among them first,
+  // digit by digit; few: they are ranked with the rest.
+  const bool tie = st[kStCstar] < (uint64_t)kSelBins - 1 &&
+                   st[kStEqual] > 4 * st[kStNeed] + (1u << 20);
+  if (tie) {
+    for (int d = 0; d < 2 * NG; ++d) {
+      hipLaunchKernelGGL(k_tie_hist<NG>, dim3(walkers), dim3(1024), 0, s, u, ts.pbits, d);
+      hipLaunchKernelGGL(k_tie_pick, dim3(1), dim3(512), 0, s, a, d);
+    }
+    BUILD_HIP(hipGetLastError(), "tie launches");
+  }
+  const uint64_t nrec = tie ? ranks : st[kStAbove] + st[kStEqual];
+  R* rec = sc.get<R>(nrec);
+  R* rec2 = sc.get<R>(nrec);
+  if (!rec || !rec2) return fail(TFE_ERR_OOM, "rank arrays");
+  hipLaunchKernelGGL(k_gather<NG>, dim3(walkers), dim3(1024), 0, s, u, ts.pbits, tie ? 1u : 0u, rec,
+                     (uint32_t)nrec);
+  BUILD_HIP(hipGetLastError(), "record launches");
+  // 5. Ranks [skip, ranks).
+  const uint64_t m = ranks - skip;
+  if (nrec <= kBucketCap / 2) {
+    hipLaunchKernelGGL(k_bk_sort<R>, dim3(1), dim3(1024), 0, s, a, rec, (uint32_t)nrec, skip, ranks,
+                       NG, out_tuples, out_counts);
+  } else if (nrec <= bucket_sort_max<R>()) {
+    uint32_t nb = 2;
+    while (nb < max_buckets<R>() && nrec / nb > kBucketMean) nb <<= 1;
+    // The remainders and their counts are no longer needed: their arrays
+    // hold the splitters and every record's bucket.
+    R* split = sc.get<R>(nb);
+    uint16_t* bkt = sc.get<uint16_t>(nrec);
+    if (!split || !bkt) return fail(TFE_ERR_OOM, "rank arrays");
+    const uint32_t tiles = blocks_for(nrec, kBkTile);
+    hipLaunchKernelGGL(k_bk_sample<R>, dim3(1), dim3(1024), 0, s, rec, nrec, nb, split);
+    hipLaunchKernelGGL(k_bk_hist<R>, dim3(tiles), dim3(1024), 0, s, a, rec, nrec, nb, split, bkt);
+    hipLaunchKernelGGL(k_bk_scatter<R>, dim3(tiles), dim3(1024), 0, s, a, rec, nrec, nb, bkt, rec2);
+    hipLaunchKernelGGL(k_bk_sort<R>, dim3(nb), dim3(1024), 0, s, a, rec2, 0u, skip, ranks, NG,
+                       out_tuples, out_counts);
+  } else {
+    uint64_t *hi = (uint64_t*)rec, *hi2 = (uint64_t*)rec2, *lo = nullptr, *lo2 = nullptr;
+    uint32_t* rhist = sc.get<uint32_t>((uint64_t)kBins * blocks_for(nrec, kTileThreads * 6));
+    if (!rhist) return fail(TFE_ERR_OOM, "rank arrays");
+    if (sizeof(R) == 16) {
+      hi = sc.get<uint64_t>(nrec);
+      lo = sc.get<uint64_t>(nrec);
+      if (!hi || !lo) return fail(TFE_ERR_OOM, "rank arrays");
+      hipLaunchKernelGGL(k_split_rec2, dim3(blocks_for(nrec, 256)), dim3(256), 0, s, (const Rec2*)rec,
+                         nrec, hi, lo);
+      lo2 = hi2 + nrec;  // rec2's bytes hold both spare arrays
+      BUILD_HIP(radix_sort<true>(lo, lo2, hi, hi2, nrec, 36, rhist, part, s), "rank sort");
+      BUILD_HIP(radix_sort<true>(hi, hi2, lo, lo2, nrec, 64, rhist, part, s), "rank sort");
+    } else {
+      BUILD_HIP(radix_sort<false>(hi, hi2, lo, lo2, nrec, 64, rhist, part, s), "rank sort");
+    }
+    hipLaunchKernelGGL(k_unpack, dim3(blocks_for(m, 256)), dim3(256), 0, s, hi, lo, skip, m, NG,
+                       out_tuples, out_counts);
+  }
+  BUILD_HIP(hipGetLastError(), "rank launches");
+  BUILD_HIP(hipStreamSynchronize(s), "sync");
+  *written = (int64_t)m;
+  return TFE_OK;
+}
 
 tfe_status ngram_top(const int32_t* tokens, int64_t N, int32_t vocab, int32_t n, int64_t skip,
                      int64_t top, int32_t* out_tuples, int64_t* out_counts, int64_t* written,
                      hipStream_t s) {
   if (!written) return fail(TFE_ERR_INVALID_ARG, "null written");
   *written = 0;
-  // The two-level scans cover up to 2^28 elements.
+  // The two-level scans cover up to 2^28 elements, a record 28-bit counts.
   if (N < 0 || N > (1ll << 28)) return fail(TFE_ERR_INVALID_ARG, "N outside [0, 2^28]");
   if (vocab < 1 || vocab > (1 << 18)) return fail(TFE_ERR_INVALID_ARG, "vocab outside [1, 2^18]");
   if (n < 1 || n > 4) return fail(TFE_ERR_UNSUPPORTED, "n = %d (1..4 supported)", n);
@@ -994,142 +1478,16 @@ tfe_status ngram_top(const int32_t* tokens, int64_t N, int32_t vocab, int32_t n,
     if (st != TFE_OK) return st;
   }
   const uint64_t nwin = (uint64_t)(N - n + 1);
-  const bool wide = n == 4;
-  Scratch sc(s);
-  uint64_t* keys = sc.get<uint64_t>(nwin);
-  uint64_t* keys_alt = sc.get<uint64_t>(nwin);
-  // 4-grams: the high word, payload of the low-word sort, then keys.
-  uint32_t* wv = wide ? sc.get<uint32_t>(nwin) : nullptr;
-  uint32_t* wv_alt = wide ? sc.get<uint32_t>(nwin) : nullptr;
-  uint32_t* hi = nullptr;
-  uint32_t* hi_alt = nullptr;
-  const uint32_t ntiles = blocks_for(nwin, kMinTile);
-  uint32_t* hist = sc.get<uint32_t>((uint64_t)kBins * ntiles);
-  uint32_t* part = sc.get<uint32_t>(kScanBlock);
-  unsigned long long* d_count = sc.get<unsigned long long>(1);
-  uint32_t* d_small = sc.get<uint32_t>(8);
-  uint32_t* sel_bins = sc.get<uint32_t>(kSelBins);
-  if (!keys || !keys_alt || !hist || !part || !d_count || !d_small || !sel_bins ||
-      (wide && (!wv || !wv_alt)))
-    return fail(TFE_ERR_OOM, "n-gram scratch for %llu windows", (unsigned long long)nwin);
-  // 1-2. keys of all windows, formed by the first radix pass, sorted (one
-  // bit above the key fields carries the invalid-window mark); the valid
-  // keys are the first M.  4-grams sort by the low word, then stably by the
-  // high word (LSD over both words).
-  uint64_t* no_vals = nullptr;
-  uint64_t* no_vals2 = nullptr;
-  // Invalid windows: with vocab < 2^18 the oldest-token field holds vocab
-  // (above every valid token), so the keys keep 18 n bits; with vocab =
-  // 2^18 one more bit above the fields.
-  const bool narrow = vocab < (1 << 18);
-  const uint64_t mark = narrow ? (uint64_t)vocab << (18 * (n - 1)) : 1ull << (18 * n);
-  const uint32_t mark4 = narrow ? (uint32_t)vocab : (1u << 18);
-  const TokSrc ts{tokens, n, vocab, mark, mark4};
-  if (!wide) {
-    const int bits = 18 * n + (narrow ? 0 : 1);
-    hipError_t e = n == 1   ? radix_sort<uint64_t, false, 1>(keys, keys_alt, no_vals, no_vals2,
-                                                             nwin, bits, hist, part, s, ts)
-                   : n == 2 ? radix_sort<uint64_t, false, 2>(keys, keys_alt, no_vals, no_vals2,
-                                                             nwin, bits, hist, part, s, ts)
-                            : radix_sort<uint64_t, false, 3>(keys, keys_alt, no_vals, no_vals2,
-                                                             nwin, bits, hist, part, s, ts);
-    BUILD_HIP(e, "key sort");
-    hipLaunchKernelGGL(k_count_valid, dim3(1), dim3(1), 0, s, keys, nwin, mark, d_count);
-  } else {
-    BUILD_HIP((radix_sort<uint64_t, true, kSrcNgram4, uint32_t>(keys, keys_alt, wv, wv_alt, nwin,
-                                                                54, hist, part, s, ts)),
-              "low-word sort");
-    hi = wv;  // the high words, now in low-word order, become the keys
-    hi_alt = wv_alt;
-    BUILD_HIP((radix_sort<uint32_t, true>(hi, hi_alt, keys, keys_alt, nwin, narrow ? 18 : 19,
-                                          hist, part, s)),
-              "high-word sort");
-    hipLaunchKernelGGL(k_count_valid_hi, dim3(1), dim3(1), 0, s, hi, nwin, mark4, d_count);
+  // Ranks beyond the number of windows do not exist (and the sum cannot
+  // overflow).
+  if ((uint64_t)skip >= nwin) return TFE_OK;
+  const uint64_t t = std::min<uint64_t>((uint64_t)top, nwin);
+  switch (n) {
+    case 1: return ngram_top_n<1>(tokens, nwin, vocab, skip, t, out_tuples, out_counts, written, s);
+    case 2: return ngram_top_n<2>(tokens, nwin, vocab, skip, t, out_tuples, out_counts, written, s);
+    case 3: return ngram_top_n<3>(tokens, nwin, vocab, skip, t, out_tuples, out_counts, written, s);
+    default: return ngram_top_n<4>(tokens, nwin, vocab, skip, t, out_tuples, out_counts, written, s);
   }
-  BUILD_HIP(hipGetLastError(), "count launch");
-  unsigned long long m_host = 0;
-  BUILD_HIP(hipMemcpyAsync(&m_host, d_count, sizeof m_host, hipMemcpyDeviceToHost, s), "copy");
-  BUILD_HIP(hipStreamSynchronize(s), "sync");
-  const uint64_t M = m_host;
-  if (M == 0) return TFE_OK;
-  // 3. runs.
-  const uint32_t nbr = blocks_for(M, kScanBlock);
-  if (wide)
-    hipLaunchKernelGGL(k_runs_reduce<true>, dim3(nbr), dim3(kScanThreads), 0, s, keys, hi, M, part);
-  else
-    hipLaunchKernelGGL(k_runs_reduce<false>, dim3(nbr), dim3(kScanThreads), 0, s, keys, hi, M,
-                       part);
-  hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(kScanThreads), 0, s, part, nbr, d_small);
-  BUILD_HIP(hipGetLastError(), "run count launches");
-  uint32_t U = 0;
-  BUILD_HIP(hipMemcpyAsync(&U, d_small, sizeof U, hipMemcpyDeviceToHost, s), "copy");
-  BUILD_HIP(hipStreamSynchronize(s), "sync");
-  uint64_t* ukey = sc.get<uint64_t>(U);
-  uint32_t* uhi = wide ? sc.get<uint32_t>(U) : nullptr;
-  uint32_t* ustart = sc.get<uint32_t>(U);
-  uint32_t* ucnt = sc.get<uint32_t>(U);
-  if (!ukey || !ustart || !ucnt || (wide && !uhi)) return fail(TFE_ERR_OOM, "run arrays");
-  if (wide)
-    hipLaunchKernelGGL(k_runs_write<true>, dim3(nbr), dim3(kScanThreads), 0, s, keys, hi, M, part,
-                       ukey, uhi, ustart);
-  else
-    hipLaunchKernelGGL(k_runs_write<false>, dim3(nbr), dim3(kScanThreads), 0, s, keys, hi, M, part,
-                       ukey, uhi, ustart);
-  BUILD_HIP(hipMemsetAsync(sel_bins, 0, kSelBins * sizeof(uint32_t), s), "memset");
-  hipLaunchKernelGGL(k_run_counts, dim3(blocks_for(U, 16384)), dim3(1024), 0, s, ustart, U,
-                     (uint32_t)M, ucnt, sel_bins);
-  BUILD_HIP(hipGetLastError(), "run launches");
-  const uint64_t R = std::min<uint64_t>((uint64_t)skip + (uint64_t)top, U);
-  if (R <= (uint64_t)skip) return TFE_OK;
-  // 4. the R-th largest count and the runs that make ranks [0, R): from the
-  // small-count histogram when it lies below kSelBins - 1, else by a radix
-  // select over the counts (its passes return at once when done).
-  uint32_t* selh = hist;  // 256 bins, cleared by each pick
-  const uint32_t state0[5] = {0u, 0u, (uint32_t)R, 0u, 0u};
-  BUILD_HIP(hipMemsetAsync(selh, 0, 256 * sizeof(uint32_t), s), "memset");
-  BUILD_HIP(hipMemcpyAsync(d_small, state0, sizeof state0, hipMemcpyHostToDevice, s), "copy");
-  hipLaunchKernelGGL(k_sel_small, dim3(1), dim3(1024), 0, s, sel_bins, d_small);
-  // The R largest counts add up to at most M, so the R-th largest is at
-  // most M / R: below kSelBins - 1 the small-count histogram has found it
-  // for certain, and the radix passes (which would return at once, at
-  // about 5 us per launch) are not launched.
-  if (M / R >= (uint64_t)kSelBins - 1) {
-    // Few blocks: each adds its LDS histogram to the 256 global bins once.
-    const uint32_t sel_blocks = std::min<uint32_t>(blocks_for(U, 256), 512);
-    for (int shift = 24; shift >= 0; shift -= 8) {
-      hipLaunchKernelGGL(k_sel_hist, dim3(sel_blocks), dim3(256), 0, s, ucnt, U, d_small, shift,
-                         selh);
-      hipLaunchKernelGGL(k_sel_pick, dim3(1), dim3(256), 0, s, selh, d_small, shift);
-    }
-  }
-  BUILD_HIP(hipGetLastError(), "select launches");
-  // state = {c*, ~0, needed runs with count c*, runs above c*}.
-  uint32_t* rkey = sc.get<uint32_t>(R);
-  uint32_t* rkey_alt = sc.get<uint32_t>(R);
-  uint64_t* rval = sc.get<uint64_t>(R);
-  uint64_t* rval_alt = sc.get<uint64_t>(R);
-  if (!rkey || !rkey_alt || !rval || !rval_alt) return fail(TFE_ERR_OOM, "rank arrays");
-  // Per-block numbers in the radix histogram buffer (idle until the rank
-  // sort; it holds kBins x ntiles >= 2 x blocks entries).
-  const uint32_t nbs = blocks_for(U, kScanBlock);
-  uint32_t* part_gt = hist;
-  uint32_t* part_eq = hist + nbs;
-  hipLaunchKernelGGL(k_sel_count, dim3(nbs), dim3(kScanThreads), 0, s, ucnt, U, d_small, part_gt,
-                     part_eq);
-  hipLaunchKernelGGL(k_sel_place, dim3(nbs), dim3(kScanThreads), 0, s, ucnt, U, d_small, part_gt,
-                     part_eq, (uint32_t)R, rkey, rval);
-  BUILD_HIP(hipGetLastError(), "selection launches");
-  // 5. rank by count (stable: tuple order among equal counts).
-  BUILD_HIP((radix_sort<uint32_t, true>(rkey, rkey_alt, rval, rval_alt, R, 32, hist, part, s)),
-            "rank sort");
-  // 6. ranks [skip, R).
-  const uint64_t m = R - (uint64_t)skip;
-  hipLaunchKernelGGL(k_unpack, dim3(blocks_for(m, 256)), dim3(256), 0, s, rkey, rval, ukey, uhi,
-                     (uint64_t)skip, m, n, out_tuples, out_counts);
-  BUILD_HIP(hipGetLastError(), "unpack launch");
-  BUILD_HIP(hipStreamSynchronize(s), "sync");
-  *written = (int64_t)m;
-  return TFE_OK;
 }
 
 }  // namespace
