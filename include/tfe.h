@@ -281,10 +281,14 @@ tfe_status tfe_head_create(const void *w_pref, int32_t vocab, int32_t dim, int32
  * 0 <= B <= max_batch, 0 <= K <= max_k; stream-ordered on `stream`.  Calls
  * on one head share its scratch: they must be ordered (same stream, or
  * synchronised).
- * Calls of at most 64 rows with K at most the number of compute units (a
- * power of two up to 256; at most 48 16-token tiles per compute unit)
- * take a one-launch path, also under stream capture: one block per
- * compute unit keeps its logits in registers, and two device-wide barriers
+ * A call takes two launches (logits, then the per-row selection), also under
+ * stream capture; on another stream than the head's previous call it waits on
+ * the device for that call.  Calls of 17 to 64 rows over 2^17 tokens or more
+ * with K at most the number of compute units (a power of two up to 256; at
+ * most 48 16-token tiles per compute unit) take a one-launch path, as does
+ * every call of at most 64 rows with such a K while the environment variable
+ * TFE_HEAD_WAIT_LIMIT is set: one block per compute unit keeps its logits in
+ * registers, and two device-wide barriers
  * inside the launch replace the write of the logits.  Its blocks must all
  * be resident at once: the library runs the one-launch calls of all heads
  * on a device one after another (each waits on the device for the previous
@@ -294,18 +298,17 @@ tfe_status tfe_head_create(const void *w_pref, int32_t vocab, int32_t dim, int32
  * head on another stream), and such
  * a call must not overlap on the device with other work that holds compute
  * units while waiting for it.  Its waits are bounded
- * (about a second); if one runs out,
- * that call's top_ids are all -1 and its top_prob 0.  Other calls take two
- * launches (logits, then the per-row selection), which have no such
- * requirement. */
+ * (about a second, or as many polls as TFE_HEAD_WAIT_LIMIT says); if one
+ * runs out, that call's top_ids are all -1 and its top_prob 0.  The two
+ * launches have no such requirement. */
 tfe_status tfe_head_topk(tfe_head *head, const void *hidden, int32_t B, int32_t K,
                          int32_t *top_ids, float *top_prob, void *stream);
 
-/* *call = the number, counted from 1 over the head's one-launch calls, of
- * the latest one-launch call whose barrier waits gave up (its top_ids all
- * -1 and its top_prob 0), or 0 if none has.  Waits for the head's last call
- * made outside stream capture first; calls replayed from a graph count like
- * the others.  For callers that cannot read every call's ids back. */
+/* *call = the number, counted from 1 over the head's calls, of the latest
+ * one-launch call whose barrier waits gave up (its top_ids all -1 and its
+ * top_prob 0), or 0 if none has.  Waits for the head's last call made
+ * outside stream capture first; calls replayed from a graph count like the
+ * others.  For callers that cannot read every call's ids back. */
 tfe_status tfe_head_last_fault(tfe_head *head, int64_t *call);
 
 /* Releases a head (waits for its last call made outside stream capture
@@ -324,7 +327,7 @@ tfe_status tfe_head_free(tfe_head *head);
  *   top_ids DEVICE int32 [B x K], top_prob DEVICE float32 [B x K].
  * Limits: 0 <= B <= 64, 1 <= vocab <= 2^18, 0 <= K <= min(256, vocab), dim
  * 256, 512 or 1024; larger sizes return TFE_ERR_INVALID_ARG.  The scratch
- * (logits, tile statistics and the logits blocks' maxima: 76.5 MiB) is a
+ * (logits, tile keys and the logits blocks' maxima and sums: 68.5 MiB) is a
  * static device array that every GPU the library runs on holds until the
  * process ends; the call allocates nothing.  A device with more than 1024
  * compute units is refused (TFE_ERR_UNSUPPORTED).  Every call on one GPU shares that GPU's scratch: calls that

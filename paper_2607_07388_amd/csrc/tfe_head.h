@@ -14,15 +14,15 @@ struct HeadArgs {
   const void* w;        // [V x D] bf16, row-major
   const void* hidden;   // [B x D] bf16
   // Scratch: groups of 64 rows (B rounded up), tpitch 16-token tiles per
-  // group (V rounded up to 32, over 16), tblocks = tpitch / 16 rounded up.
+  // group (V rounded up to 32, over 16), tblocks = tpitch / 32 rounded up.
   float* logits;        // [groups x tpitch x 64 x 16], tile-major
-  uint64_t* tkey;       // [groups x tblocks x 64 x 16]: largest (logit, id) key per tile
-  float* tsum;          // [groups x tblocks x 64 x 16]: sum of exp(logit - tile max)
-  uint64_t* bmax;       // [groups x nblk x 64]: largest tile key per (logits block, row)
+  uint32_t* tkey;       // [groups x tblocks x 64 x 32]: key of the largest logit per tile
+  uint32_t* bmax;       // [groups x nblk x 64]: largest tile key per (logits block, row)
+  float* bexp;          // [groups x nblk x 64]: its sum of exp(logit - that largest logit)
   int32_t* top_ids;     // [B x K]
   float* top_prob;      // [B x K]
   uint32_t V, tpitch, tblocks, D, B, K;
-  uint32_t nblk;        // logits blocks per 64-row group (one per compute unit)
+  uint32_t nblk;        // logits blocks (one per compute unit, at most 1024)
   // One-launch path (B <= 64; see launch_head_fused): per (row, logits
   // block) the high word of the block's largest key (0: no logits) and its
   // sum of exp(logit - that logit); per (row, block) a segment of ccap
@@ -32,16 +32,19 @@ struct HeadArgs {
   uint32_t* bsum;       // [64 x nblk], float bits
   uint64_t* cand;       // [64 x nblk x ccap]
   unsigned long long* bar;
-  unsigned long long* fault;  // the last faulted call's epoch + 1
+  unsigned long long* fault;  // number of the last call that gave up
+  unsigned long long* ncall;  // two-launch calls on this head so far (may be null)
   uint32_t ccap;        // 1 + 16 x the most tiles a block owns, rounded up to 16
   unsigned long long* ectl;  // [16 i], i < 16: blocks of earlier one-launch calls
                              // on this scratch that have left (block b adds to b mod 16)
   uint32_t wait_limit;  // polls before a barrier wait gives up (kHeadWaitLimit)
 };
 
+
 // Polls of a one-launch barrier before it gives up (about a second).  The
-// environment variable TFE_HEAD_WAIT_LIMIT overrides it per call, so that
-// tests can force the give-up path from the host.
+// environment variable TFE_HEAD_WAIT_LIMIT overrides it per call, and while it
+// is set every call that fits the one-launch kernel takes it, so that tests
+// can force the give-up path from the host.
 constexpr uint32_t kHeadWaitLimit = 1u << 20;
 
 // True if D has a logits kernel.
@@ -56,6 +59,15 @@ hipError_t launch_head_rows(const HeadArgs& a, hipStream_t s);
 // B and K at most nblk, nblk a power of two <= 256, at most 48 tiles per
 // block).
 bool head_fused_fits(const HeadArgs& a);
+// True where one launch is the faster way for a call that fits it: many rows
+// and a large vocabulary, so that the logits' write outweighs the two grid
+// barriers.  Two launches / one, us, at dim 1024 with rotating projections:
+//   151936 tokens: 64 rows, K = 128: 78.4 / 74.2; 32 rows, K = 64: 71.1 / 69.9;
+//                  16 rows, K = 64: 65.4 / 69.3; one row 64 / 68
+//   120000 tokens: 66.1 / 67.6; 59.7 / 63.4; 57.0 / 61.6
+//    50000 tokens: 64 rows 38.8 / 46.1, one row 31.3 / 38.9
+// (dim 256, 151936 tokens: 41.5 / 39.8; 34.7 / 35.5; 31.4 / 34.9).
+bool head_fused_faster(const HeadArgs& a);
 // Words per (row, block) segment of the candidate scratch for this vocabulary.
 uint32_t head_fused_ccap(uint32_t V, uint32_t nblk);
 // True if a block of the one-launch kernel for D fits a compute unit of the

@@ -3,35 +3,33 @@
 // (Eq. 13) and its K most likely tokens (Eq. 14), which are the candidates
 // the cache prefetch consumes.
 //
-// For up to 64 rows (and K at most the number of compute units) one launch,
-// k_head_fused (below, with its design); otherwise two launches:
-//   k_head_logits  logits = W h for up to 64 rows h per block: a dense
+// Two launches:
+//   k_head_logits  logits = W h for up to 256 rows h per block: a dense
 //                  contraction, so it runs on the matrix cores
-//                  (v_mfma_f32_16x16x32_bf16).  W ([V x D] bf16, 311 MB for
-//                  the 151936 x 1024 head) is streamed from HBM exactly once
-//                  per 64 rows; the 64 hidden rows are staged in LDS and read
-//                  by every wave.  One wave computes three 16-token x
-//                  64-row tiles at a time (single tiles for the rest of a
-//                  block's range), which share each read of the staged
-//                  rows: W is read 128 contiguous bytes per row and load
-//                  instruction, a few chunks of every row in flight
-//                  together, then passed through a small per-wave LDS
-//                  staging tile into the MFMA operand layout.
-//                  The epilogue writes the fp32 logits and, per (row,
-//                  16-token tile), the largest (logit, id) key and the sum of
-//                  exp(logit - tile max).
-//   k_head_rows    per row: the log-sum-exp from the tile statistics, a
+//                  (v_mfma_f32_16x16x32_bf16), with W ([V x D] bf16, 311 MB for
+//                  the 151936 x 1024 head) streamed from HBM once (its design
+//                  below).  The epilogue writes the fp32 logits and, per (row,
+//                  16-token tile), the key of the largest logit; per (row,
+//                  block) the largest key and the sum of exp(logit - largest).
+//   k_head_rows    per row: the log-sum-exp from the blocks' sums, a
 //                  radix select over the tile keys down to a set of at least
 //                  K tiles (every top-K logit lies in one of the K tiles with
-//                  the largest maxima), then those tiles' logits ranked in
-//                  LDS.
+//                  the largest maxima, equal maxima taken in tile order), then
+//                  those tiles' logits ranked in LDS.
+// For up to 64 rows, K at most the number of compute units and a large
+// vocabulary (head_fused_faster has both sides measured), one launch:
+// k_head_fused (below, with its design).
 // Ties in logit go to the lower token id, so the answer is unique.  The K
 // output probabilities use the full-accuracy expf (about 1 ulp); the chunk
 // sums of exp(l - max) use the hardware exponential, whose relative error
 // (about |l - max| 2^-24 plus an ulp) is negligible in a sum dominated by
 // terms near the maximum.
 #include <hip/hip_runtime.h>
+#include <float.h>
 #include <stdint.h>
+
+#include <algorithm>
+#include <type_traits>
 
 #include "tfe_head.h"
 
@@ -60,9 +58,6 @@ __device__ __forceinline__ uint32_t f2key(float f) {
 __device__ __forceinline__ float key2f(uint32_t k) {
   return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
 }
-// 64-bit unsigned max (the generic max/min overloads can resolve to
-// floating point for mixed integer types, which would round the keys).
-__device__ __forceinline__ uint64_t umax64(uint64_t x, uint64_t y) { return x > y ? x : y; }
 // (logit, token) -> 64-bit key: higher logit first, then lower token id.
 // Keys are distinct, and 0 is below every real key.
 __device__ __forceinline__ uint64_t tkey64(float l, uint32_t id) {
@@ -73,66 +68,18 @@ __device__ __forceinline__ uint64_t tkey64(float l, uint32_t id) {
 // MFMA output column: permlane16_swap pairs rows 0-1 and 2-3 of the wave,
 // permlane32_swap pairs the two halves; combining both outputs of each swap
 // leaves every lane with the reduction in a fixed order.
-__device__ __forceinline__ uint64_t col_max64(uint64_t k) {
-  uint32_t hi = (uint32_t)(k >> 32), lo = (uint32_t)k;
-  const auto h16 = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-  const auto l16 = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-  k = umax64(((uint64_t)h16[0] << 32) | l16[0], ((uint64_t)h16[1] << 32) | l16[1]);
-  hi = (uint32_t)(k >> 32);
-  lo = (uint32_t)k;
-  const auto h32 = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-  const auto l32 = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-  return umax64(((uint64_t)h32[0] << 32) | l32[0], ((uint64_t)h32[1] << 32) | l32[1]);
-}
-__device__ __forceinline__ float col_sum(float x) {
-  uint32_t u = __float_as_uint(x);
+__device__ __forceinline__ uint32_t col_max32(uint32_t u) {
   const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  u = __float_as_uint(__uint_as_float(a[0]) + __uint_as_float(a[1]));
+  u = max(a[0], a[1]);
   const auto b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+  return max(b[0], b[1]);
 }
-
-// Stores one 16-token x 64-row tile of logits and its statistics.  Logits
-// are tile-major: logits[((grp * tpitch + t) * 64 + c) * 16 + i] for column
-// c = j - 64 grp and token 16 t + i, so a tile is one contiguous 4 KB block
-// (each store instruction writes 1 KB of whole lines) and a row's 16 logits
-// of a tile are 64 contiguous bytes.  Statistics are blocked by 16 tiles:
-// entry (t, c) at ((grp * tblocks + t / 16) * 64 + c) * 16 + t % 16, so 16
-// consecutive tiles of a row fill one 128-byte line (written by the block's
-// waves close together in time, read whole by the top-K kernel).
-// D operand: lane (r, g) holds tokens t*16 + 4 g + q, q = 0..3, of column r.
-// The scratch is padded (whole 32-token super-tiles, rows up to a multiple
-// of 64), so the logits stores are in bounds and unconditional (columns
-// past B and tokens past V hold junk that nothing reads).
-__device__ __forceinline__ void tile_epilogue(const HeadArgs& a, uint32_t t, int r, int g,
-                                              const f32x4* acc, uint64_t* bm) {
-  const uint32_t i0 = t * 16 + 4 * g;
-  const size_t tile = (size_t)blockIdx.y * a.tpitch + t;
-#pragma unroll
-  for (int bt = 0; bt < 4; ++bt) {
-    const uint32_t c = bt * 16 + r;
-    // Streamed past the L2 (read back only for the few candidate tiles).
-    __builtin_nontemporal_store(acc[bt], (f32x4*)(a.logits + (tile * 64 + c) * 16 + 4 * g));
-    // Tile statistics of column c: the largest (logit, id) key of the 16
-    // tokens and the sum of exp(logit - tile max); all four lanes of the
-    // column hold the same values and the first one writes them.
-    uint64_t best = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      best = umax64(best, i0 + q < a.V ? tkey64(acc[bt][q], i0 + q) : (uint64_t)0);
-    best = col_max64(best);
-    bm[bt] = umax64(bm[bt], best);  // the wave's largest key of column c so far
-    const float m = key2f((uint32_t)(best >> 32));
-    float sum = 0.f;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) sum += i0 + q < a.V ? __expf(acc[bt][q] - m) : 0.f;
-    sum = col_sum(sum);
-    if (g == 0) {
-      const size_t o = (((size_t)blockIdx.y * a.tblocks + (t >> 4)) * 64 + c) * 16 + (t & 15);
-      a.tkey[o] = best;
-      a.tsum[o] = sum;
-    }
-  }
+// The same for four values at once: lane 16 g + r gets x_g's.
+__device__ __forceinline__ uint32_t col_max32x4(uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3) {
+  const auto a = __builtin_amdgcn_permlane16_swap(x0, x1, false, false);
+  const auto b = __builtin_amdgcn_permlane16_swap(x2, x3, false, false);
+  const auto c = __builtin_amdgcn_permlane32_swap(max(a[0], a[1]), max(b[0], b[1]), false, false);
+  return max(c[0], c[1]);
 }
 
 // One wave's logits for TPW consecutive 16-token tiles from t, accumulated
@@ -212,93 +159,335 @@ __device__ __forceinline__ void logits_acc(const HeadArgs& a, uint32_t t, uint32
   }
 }
 
-// logits_acc, then the epilogue of every tile below t_hi.
-template <int KS, int TPW, int PC>
-__device__ __forceinline__ void logits_tiles(const HeadArgs& a, uint32_t t, uint32_t t_hi,
-                                             const __bf16* hs, __bf16* st, int hoff, int lane,
-                                             int r, int g, uint64_t* bm) {
-  f32x4 acc[TPW][4];
-  logits_acc<KS, TPW, PC>(a, t, t_hi, hs, st, hoff, lane, r, g, acc);
-#pragma unroll
-  for (int i = 0; i < TPW; ++i)
-    if (t + (uint32_t)i < t_hi) tile_epilogue(a, t + i, r, g, acc[i], bm);
-}
-
-// Tiles per wave and chunks per pass of the logits kernel: three tiles
-// with two-chunk passes (12 KB in flight per wave), then single tiles with
-// four-chunk passes for the rest of a block's range.  (Measured on the
-// 151936 x 1024 head at B = 64: 88.6 us per call against 93.0 for single
-// tiles with eight-chunk passes; 2, 4 or 5 tiles, or longer passes, were
+// Tiles per wave and chunks per pass of the one-launch kernel: three tiles
+// with two-chunk passes (12 KB in flight per wave).  (Measured on the
+// 151936 x 1024 head at B = 64: 2, 4 or 5 tiles, or longer passes, were
 // slower.)
 constexpr int kTileGroup = 3;
 constexpr int kGroupChunks = 2;
-constexpr int kSingleChunks = 4;
 
-template <int KS>  // KS = D / 32 k-steps
-__global__ __launch_bounds__(kLogitWaves * 64) void k_head_logits(const HeadArgs a) {
-  constexpr int D = KS * 32;
-  constexpr int STRIDE = D + 8;  // staged hidden row pitch (elements): conflict-free b128 reads
-  constexpr int SP = 72;         // W staging row pitch (elements): conflict-free b128 reads
-  __shared__ __attribute__((aligned(16))) __bf16 hs[kCols * STRIDE];
-  __shared__ __attribute__((aligned(16))) __bf16 stage[kLogitWaves][16 * SP];
-  __shared__ uint32_t s_next, s_next1;
-  __shared__ unsigned long long s_bmax[kCols];  // the block's largest tile key per column
-  if (threadIdx.x < kCols) s_bmax[threadIdx.x] = 0;
-  const uint32_t col0 = blockIdx.y * kCols;
-  const int ncols = (int)min((uint32_t)kCols, a.B - col0);
-  for (int e = threadIdx.x; e < kCols * (D / 8); e += kLogitWaves * 64) {
-    const int j = e / (D / 8), c = e - j * (D / 8);
-    u32x4 v = {0u, 0u, 0u, 0u};
-    if (j < ncols) v = *((const u32x4*)a.hidden + ((size_t)(col0 + j) * D) / 8 + c);
-    *(u32x4*)(hs + j * STRIDE + c * 8) = v;
-  }
-  // The block owns a contiguous range of 16-token tiles; its waves claim
-  // groups of kTileGroup tiles while whole groups remain, then single
-  // tiles, so every wave stays busy until the range is done.
-  const uint32_t nt = (a.V + 15) >> 4;
-  const uint32_t t_lo = (uint32_t)((uint64_t)nt * blockIdx.x / gridDim.x);
-  const uint32_t t_hi = (uint32_t)((uint64_t)nt * (blockIdx.x + 1) / gridDim.x);
-  const uint32_t t_grp = t_lo + (t_hi - t_lo) / kTileGroup * kTileGroup;
-  if (threadIdx.x == 0) {
-    s_next = t_lo;
-    s_next1 = t_grp;
-  }
-  __syncthreads();
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int r = lane & 15, g = lane >> 4;
-  __bf16* st = stage[wave];
-  // The staged hidden rows do not change across tiles; hiding the offset
-  // from the optimiser keeps their LDS reads inside the loop (hoisted, the
-  // whole 128 KB B operand would be held in registers and spill).
-  int hoff = r * STRIDE + 8 * g;
-  uint64_t bm[4] = {0, 0, 0, 0};  // column bt * 16 + r (lanes g = 0 hold it)
-  for (;;) {
-    uint32_t t = 0;
-    if (lane == 0) t = atomicAdd(&s_next, (uint32_t)kTileGroup);
-    t = __builtin_amdgcn_readfirstlane(t);
-    if (t >= t_grp) break;
-    asm volatile("" : "+v"(hoff));
-    logits_tiles<KS, kTileGroup, kGroupChunks>(a, t, t_hi, hs, st, hoff, lane, r, g, bm);
-  }
-  for (;;) {
-    uint32_t t = 0;
-    if (lane == 0) t = atomicAdd(&s_next1, 1u);
-    t = __builtin_amdgcn_readfirstlane(t);
-    if (t >= t_hi) break;
-    asm volatile("" : "+v"(hoff));
-    logits_tiles<KS, 1, kSingleChunks>(a, t, t_hi, hs, st, hoff, lane, r, g, bm);
-  }
-  // The block's largest tile key per row (0 for a block without tiles),
-  // from which the top-K kernel certifies a lower bound of each row's K-th
-  // largest logit.
-  if (g == 0) {
+// ---- Logits of the two-launch path -----------------------------------------
+//
+// One block per compute unit owns a contiguous range of 16-token tiles and up
+// to 256 hidden rows, so W is read from HBM once for all of them (64-row
+// blocks read it four times for 256 rows: 284 us a call, now 128); the
+// work is a matrix product of V x D by D x N.  Each of the eight waves
+// computes TW tiles x N rows in registers (tiles x rows are as large as two
+// waves per SIMD can hold).  A row of W is used by one wave only, so W stays
+// in registers from its load, R chunks of 64 elements ahead of its use, until
+// it passes through the wave's LDS tile into MFMA layout; the hidden rows,
+// which every wave uses, are staged in LDS (double-buffered chunks, one
+// barrier each).  Measured at 256 rows, 151936 x 1024:
+//   - W loaded straight in MFMA layout (16 rows x 64 bytes per instruction)
+//     instead of 8 rows x 128 bytes and the LDS tile: 126 against 115 us (64
+//     rows: 72 against 58): neighbouring lanes on 16 different lines cost the
+//     L1 a lookup each;
+//   - row operands read right before their MFMAs: 143 against 134 us;
+//   - what bounds it now: the streams of W and of the logits (466 MB, 78 us at
+//     6 TB/s), which overlap only in part, the blocks being in step: without
+//     the logits' store 100 us, without the whole epilogue 85.
+constexpr int kChunk = 64;  // elements of a staged row (128 bytes, eight 16-byte pieces)
+// Where piece p of staged row r lies in the row.  A 16-byte LDS access takes
+// 16 lanes a cycle, which are not 16 consecutive ones: rows padded to 144
+// bytes met in the same banks (43% of the kernel's LDS cycles); with the
+// pieces exchanged by (r / 2) mod 8 the MFMA operand reads and the staging
+// writes are free of conflicts.
+__device__ __forceinline__ uint32_t piece_at(uint32_t r, uint32_t p) { return p ^ ((r >> 1) & 7u); }
+constexpr uint32_t kKeyBlock = 32;  // tiles per block of tile keys
+
+// Waits for this wave's LDS operations and for the block; loads from memory
+// stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// The key of the largest of four logits.  Bit patterns of floats order as
+// signed integers, the negative ones in reverse.
+__device__ __forceinline__ uint32_t max_key4(const f32x4 v) {
+  int s = __float_as_int(v[0]);
+  uint32_t u = __float_as_uint(v[0]);
 #pragma unroll
-    for (int bt = 0; bt < 4; ++bt)
-      if (bm[bt]) atomicMax(&s_bmax[bt * 16 + r], (unsigned long long)bm[bt]);
+  for (int q = 1; q < 4; ++q) {
+    s = max(s, __float_as_int(v[q]));
+    u = min(u, __float_as_uint(v[q]));
+  }
+  return s >= 0 ? (uint32_t)s | 0x80000000u : ~u;
+}
+
+// What a wave of a logits block knows throughout.
+struct LogitWave {
+  uint32_t t_hi;     // end of the block's tiles
+  uint32_t col0;     // first hidden row of the block
+  int wave, r, g;    // MFMA lane coordinates
+  const char* hid;   // hidden row col0
+  __bf16* hb;        // [2][N x kChunk] staged chunks
+  uint32_t* key;     // [waves][column tile][lane] key of the lane's largest logit (0: none)
+  float* sum;        // the same: its sum of exp(logit - that logit)
+  __bf16* st;        // [16 x kChunk] the wave's staged chunk of a tile of W
+  // Byte offset of this lane's piece of its row of half h of tile t (a tile
+  // past the block's re-reads the last; nothing uses its logits).
+  __device__ __forceinline__ uint32_t row_at(const HeadArgs& a, uint32_t t, int h) const {
+    const uint32_t lane = (uint32_t)(r + 16 * g);
+    return min(min(t, t_hi - 1) * 16 + 8 * h + (lane >> 3), a.V - 1) * (a.D * 2) + 16u * (lane & 7);
+  }
+};
+
+// Tiles per wave of the round that starts with `left` tiles to go (at most
+// TWM; the last round is the smallest that holds them).
+template <int TWM>
+__device__ __forceinline__ uint32_t round_tiles(uint32_t left) {
+  return min((left + kLogitWaves - 1) / kLogitWaves, (uint32_t)TWM);
+}
+
+// Logits and statistics of the tiles [t0, t0 + waves TW) below t_hi.  On
+// entry and on return chunk 0 of the hidden rows is staged in buffer 0, hv
+// holds this thread's pieces of chunk 1 and av the first R chunks of the
+// wave's rows of W (on return: of the next round's, on their way).  Loads
+// return in order, so each step requests its pieces of the chunk after next
+// ahead of its chunk of W: waiting for the pieces a step later leaves the
+// W loads in flight.
+template <int NT, int TW, int TWM, int R>
+__device__ __forceinline__ void logits_round(const HeadArgs& a, const LogitWave& c, uint32_t t0,
+                                             const uint32_t* hoff, u32x4 (&hv)[NT / 4],
+                                             u32x4 (&av)[R][2][TWM]) {
+  constexpr int N = 16 * NT;
+  constexpr int HC = NT / 4;  // 16-byte pieces of a chunk per thread
+  static_assert(kLogitWaves == 8, "512 threads stage N x 8 pieces");
+  static_assert(R == 2 || R == 4, "the chunks of D = 256 in whole groups, buffers in turn");
+  const uint32_t tid = threadIdx.x, nk = a.D / 64;
+  const uint32_t tw0 = t0 + (uint32_t)(c.wave * TW);
+  const bool act = tw0 < c.t_hi;  // wave-uniform; every wave but in the last round
+  const char* w = (const char*)a.w;
+  f32x4 acc[TW][NT];
+  auto steps = [&](auto busy) {
+    constexpr bool BUSY = decltype(busy)::value;
+    uint32_t off[TW][2];
+    if (BUSY) {
+#pragma unroll
+      for (int i = 0; i < TW; ++i) {
+        off[i][0] = c.row_at(a, tw0 + (uint32_t)i, 0);
+        off[i][1] = c.row_at(a, tw0 + (uint32_t)i, 1);
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+    }
+    for (uint32_t k0 = 0; k0 < nk; k0 += R) {
+      uint32_t wb = 128 * (k0 + R);  // byte offset in a row of the chunks to load
+      if (k0 + R >= nk) {
+        wb = 0;
+        if (BUSY) {
+          const uint32_t tn = t0 + (uint32_t)(kLogitWaves * TW);
+          const uint32_t twn = round_tiles<TWM>(tn < c.t_hi ? c.t_hi - tn : 0u);
+#pragma unroll
+          for (int i = 0; i < TW; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+              off[i][h] = c.row_at(a, tn + (uint32_t)c.wave * twn + (uint32_t)i, h);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < R; ++u) {
+        const char* wk = w + (wb + 128 * u);
+        const uint32_t kn = k0 + u + 2;
+        const char* hk = c.hid + 128 * (kn < nk ? kn : kn - nk);
+        const __bf16* rd = c.hb + (u & 1) * (N * kChunk) + c.r * kChunk;
+        __bf16* wr = c.hb + ((u & 1) ^ 1) * (N * kChunk) + (tid >> 3) * kChunk +
+                     8 * piece_at(tid >> 3, tid & 7);
+#pragma unroll
+        for (int q = 0; q < HC; ++q) {
+          *(u32x4*)(wr + q * 64 * kChunk) = hv[q];
+          hv[q] = *(const u32x4*)(hk + hoff[q]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (BUSY) {
+          // The chunk of W in MFMA layout, through the wave's staging tile.
+          u32x4 aw[2][TW];
+#pragma unroll
+          for (int i = 0; i < TW; ++i) {
+            const uint32_t lane = (uint32_t)(c.r + 16 * c.g), row = lane >> 3;
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+              *(u32x4*)(c.st + (8 * h + row) * kChunk + 8 * piece_at(8 * h + row, lane & 7)) =
+                  av[u][h][i];
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+              aw[x][i] = *(const u32x4*)(c.st + c.r * kChunk +
+                                         8 * piece_at((uint32_t)c.r, 4 * x + (uint32_t)c.g));
+          }
+          // Operands of the rows, in groups of four column tiles, one group
+          // ahead of its MFMAs (left alone, the scheduler reads each right
+          // before its use and waits for it).
+          constexpr int NG = NT / 2;  // (half of the chunk, four column tiles)
+          u32x4 bv[2][4];
+          auto read = [&](int q) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              bv[q & 1][j] =
+                  *(const u32x4*)(rd + (4 * (q % (NT / 4)) + j) * 16 * kChunk +
+                                  8 * piece_at((uint32_t)c.r, 4 * (q / (NT / 4)) + (uint32_t)c.g));
+          };
+          read(0);
+#pragma unroll
+          for (int q = 0; q < NG; ++q) {
+            if (q + 1 < NG) read(q + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+              for (int i = 0; i < TW; ++i) {
+                f32x4& d = acc[i][4 * (q % (NT / 4)) + j];
+                d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    __builtin_bit_cast(bf16x8, aw[q / (NT / 4)][i]),
+                    __builtin_bit_cast(bf16x8, bv[q & 1][j]), d, 0, 0, 0);
+              }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+#pragma unroll
+          for (int i = 0; i < TW; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+              av[u][h][i] = __builtin_nontemporal_load((const u32x4*)(wk + off[i][h]));
+        }
+        lds_barrier();
+      }
+    }
+  };
+  if (act) steps(std::true_type{});
+  else steps(std::false_type{});
+  if (!act) return;
+  // Logits are tile-major: logits[((grp * tpitch + t) * 64 + c) * 16 + i] for
+  // row 64 grp + c and token 16 t + i, so a tile is one contiguous 4 KB block
+  // (each store writes 1 KB of whole lines) and a row's 16 logits of a tile
+  // are 64 contiguous bytes.  Tile keys are blocked: entry (t, c) at
+  // ((grp * tblocks + t / 32) * 64 + c) * 32 + t % 32, so 32 consecutive tiles
+  // of a row fill one 128-byte line, read whole by the top-K kernel.
+  // Lane (r, g) holds tokens 16 t + 4 g + q, q = 0..3, of column tile j's row r.
+  static_assert(TW <= 4, "one tile per lane of a column");
+  const uint32_t lg = (uint32_t)(c.r * 64 + c.g * 16);  // bytes, in a column tile of logits
+  const uint32_t tg = tw0 + (uint32_t)c.g;              // the tile whose key this lane stores
+  const uint32_t lk = (((tg / kKeyBlock) * 64 + (uint32_t)c.r) * kKeyBlock + tg % kKeyBlock) * 4;
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    const uint32_t grp = (c.col0 >> 6) + j / 4, cc = j % 4 * 16;  // uniform
+    if (grp * 64 + cc >= a.B) break;  // no rows from here on
+    uint32_t kk[4], best = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t t = tw0 + (uint32_t)i;
+      kk[i] = 0;
+      if (i >= TW || t >= c.t_hi) continue;  // uniform
+      // Streamed past the L2 (read back only for the few candidate tiles).
+      char* lb = (char*)a.logits + (((size_t)grp * a.tpitch + t) * 64 + cc) * 64;
+      __builtin_nontemporal_store(acc[i][j], (f32x4*)(lb + lg));
+      if (t * 16 + 16 > a.V) {  // the vocabulary's ragged last tile: -inf past its end
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (t * 16 + 4 * (uint32_t)c.g + q >= a.V) acc[i][j][q] = -INFINITY;
+      }
+      kk[i] = max_key4(acc[i][j]);
+      best = max(best, kk[i]);
+    }
+    // The largest of the column's four lanes, tile by tile: lane g gets tile g.
+    const uint32_t kt = TW == 1 ? col_max32(kk[0]) : col_max32x4(kk[0], kk[1], kk[2], kk[3]);
+    char* kb = (char*)a.tkey + ((size_t)grp * a.tblocks * 64 + cc) * kKeyBlock * 4;
+    if (c.g < TW && tg < c.t_hi) *(uint32_t*)(kb + lk) = kt;
+    // The lane's sum goes on from its earlier rounds.  (The reference is
+    // finite for a lane whose tokens all lie past the vocabulary.)
+    const uint32_t o = ((uint32_t)c.wave * NT + j) * 64 + (uint32_t)(c.r + 16 * c.g);
+    const uint32_t k0 = c.key[o], k1 = max(k0, best);
+    const float m = fmaxf(key2f(k1), -FLT_MAX);
+    float s = k0 ? c.sum[o] * __expf(key2f(k0) - m) : 0.f;  // (exp(-inf) times 0 is 0)
+#pragma unroll
+    for (int i = 0; i < TW; ++i) {
+      if (tw0 + (uint32_t)i >= c.t_hi) continue;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) s += __expf(acc[i][j][q] - m);
+    }
+    c.key[o] = k1;
+    c.sum[o] = s;
+  }
+}
+
+template <int NT, int TWM, int R>
+__global__ __launch_bounds__(kLogitWaves * 64) void k_head_logits(const HeadArgs a) {
+  constexpr int N = 16 * NT, HC = N / 64;
+  __shared__ __attribute__((aligned(16))) __bf16 hb[2][N * kChunk];
+  __shared__ __attribute__((aligned(16))) __bf16 stage[kLogitWaves][16 * kChunk];
+  __shared__ uint32_t s_key[kLogitWaves * NT * 64];
+  __shared__ float s_sum[kLogitWaves * NT * 64];
+  const uint32_t tid = threadIdx.x;
+  const int lane = tid & 63;
+  LogitWave c;
+  c.col0 = blockIdx.y * N;
+  c.wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  c.r = lane & 15;
+  c.g = lane >> 4;
+  c.hid = (const char*)a.hidden + (size_t)c.col0 * a.D * 2;
+  c.hb = &hb[0][0];
+  c.st = stage[c.wave];
+  c.key = s_key;
+  c.sum = s_sum;
+#pragma unroll
+  for (int j = 0; j < NT; ++j) s_key[(c.wave * NT + j) * 64 + lane] = 0;
+  // Piece q of a thread: 16 bytes of row tid / 8 + 64 q of the chunk (rows
+  // past the last re-read it; nothing reads their logits).
+  const uint32_t ncols = min((uint32_t)N, a.B - c.col0);
+  uint32_t hoff[HC];
+  u32x4 hv[HC];
+#pragma unroll
+  for (int q = 0; q < HC; ++q) {
+    hoff[q] = min((tid >> 3) + 64u * q, ncols - 1) * (a.D * 2) + (tid & 7) * 16;
+    *(u32x4*)(c.hb + ((tid >> 3) + 64 * q) * kChunk + 8 * piece_at(tid >> 3, tid & 7)) =
+        *(const u32x4*)(c.hid + hoff[q]);
+    hv[q] = *(const u32x4*)(c.hid + 128 + hoff[q]);
+  }
+  const uint32_t nt = (a.V + 15) >> 4;
+  uint32_t t = (uint32_t)((uint64_t)nt * blockIdx.x / gridDim.x);
+  c.t_hi = (uint32_t)((uint64_t)nt * (blockIdx.x + 1) / gridDim.x);
+  __syncthreads();
+  if (t < c.t_hi) {  // block-uniform
+    u32x4 av[R][2][TWM];
+    const uint32_t tw = round_tiles<TWM>(c.t_hi - t);
+#pragma unroll
+    for (int i = 0; i < TWM; ++i) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const char* w = (const char*)a.w + c.row_at(a, t + (uint32_t)c.wave * tw + (uint32_t)i, h);
+#pragma unroll
+        for (int u = 0; u < R; ++u)
+          av[u][h][i] = __builtin_nontemporal_load((const u32x4*)(w + 128 * u));
+      }
+    }
+    for (; t + kLogitWaves * (TWM - 1) < c.t_hi; t += kLogitWaves * TWM)
+      logits_round<NT, TWM, TWM, R>(a, c, t, hoff, hv, av);
+    if (t < c.t_hi) {
+      const uint32_t tl = round_tiles<TWM>(c.t_hi - t);  // below TWM
+      if (TWM > 3 && tl == 3) logits_round<NT, TWM - 1, TWM, R>(a, c, t, hoff, hv, av);
+      else if (TWM > 2 && tl == 2) logits_round<NT, 2, TWM, R>(a, c, t, hoff, hv, av);
+      else logits_round<NT, 1, TWM, R>(a, c, t, hoff, hv, av);
+    }
   }
   __syncthreads();
-  if (threadIdx.x < kCols)
-    a.bmax[((size_t)blockIdx.y * a.nblk + blockIdx.x) * kCols + threadIdx.x] = s_bmax[threadIdx.x];
+  // The key of the block's largest logit per row (0 for a block without
+  // tiles), from which the top-K kernel certifies a lower bound of each row's
+  // K-th largest logit, and the block's sum of exp(logit - that logit).
+  if (tid < (uint32_t)N && c.col0 + tid < a.B) {
+    const uint32_t e = (tid >> 4) * 64 + (tid & 15);
+    uint32_t k = 0;
+#pragma unroll
+    for (int m = 0; m < kLogitWaves * 4; ++m)
+      k = max(k, s_key[(m >> 2) * NT * 64 + e + 16 * (m & 3)]);
+    float s = 0.f;
+#pragma unroll
+    for (int m = 0; m < kLogitWaves * 4; ++m) {
+      const uint32_t q = (m >> 2) * NT * 64 + e + 16 * (m & 3), kq = s_key[q];
+      if (kq) s += s_sum[q] * __expf(key2f(kq) - fmaxf(key2f(k), -FLT_MAX));
+    }
+    const uint32_t col = c.col0 + tid;
+    const size_t o = ((size_t)(col >> 6) * a.nblk + blockIdx.x) * 64 + (col & 63);
+    a.bmax[o] = k;
+    a.bexp[o] = s;
+  }
 }
 
 // Wave-wide reductions and scans with DPP (rows of 16 lanes) and readlane,
@@ -403,7 +592,7 @@ __device__ __forceinline__ void list_tiles(const uint64_t (&key)[NI], uint32_t N
 
 // Per row: the K most likely tokens and their probabilities from the tile
 // statistics and the logits.
-//   1. M = max logit, S = sum over tiles of tsum * exp(tile max - M).
+//   1. M = max logit, S = sum over logits blocks of bexp * exp(block max - M).
 //   2. A lower bound of the K-th largest logit from the logits blocks'
 //      largest keys (one 8-bit histogram of 256 values) usually lists the
 //      candidate tiles in one pass.  Otherwise a radix select over the
@@ -435,28 +624,31 @@ __global__ __launch_bounds__(kRowThreads) void k_head_rows(const HeadArgs a) {
     s_ntile = 0;
     s_nc = 0;
     s_lo = 0;
+    // One more two-launch call of the head.
+    if (b == 0 && a.ncall)
+      (void)__hip_atomic_fetch_add(a.ncall, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   const uint32_t NT = (a.V + 15) >> 4;
-  // Statistics of tile t of this row: block t / 16 of the row's 64-row
-  // group, column c, slot t % 16.
+  // Key of tile t of this row: block t / 32 of the row's 64-row group, column
+  // c, slot t % 32.
   const size_t grp = b >> 6, c = b & 63;
-  const uint64_t* tk = a.tkey + (grp * a.tblocks * 64 + c) * 16;
-  const float* ts = a.tsum + (grp * a.tblocks * 64 + c) * 16;
-  auto sidx = [](uint32_t t) { return (size_t)(t >> 4) * 1024 + (t & 15); };
+  const uint32_t* tk = a.tkey + (grp * a.tblocks * 64 + c) * kKeyBlock;
+  auto sidx = [](uint32_t t) { return (size_t)(t / kKeyBlock) * (64 * kKeyBlock) + t % kKeyBlock; };
 
-  // Tile keys and sums, and the logits blocks' largest keys of this row
-  // (step 2a), are loaded together (one round trip).
+  // Tile keys, and the logits blocks' largest keys and sums of this row
+  // (steps 1 and 2a), are loaded together (one round trip).
   const uint32_t take = min(a.K, NT);
-  const bool bound = take < NT && a.K <= a.nblk && a.nblk <= (uint32_t)kRowThreads;
-  const uint64_t bmv = bound && (uint32_t)tid < a.nblk
-                           ? a.bmax[(grp * a.nblk + (uint32_t)tid) * 64 + c] : 0;  // 0: none
+  const bool bound = take < NT && a.K <= a.nblk;
+  const size_t bo = (grp * a.nblk + (uint32_t)tid) * 64 + c;
+  // 0: none (nblk <= kRowThreads).
+  const uint64_t bmv = (uint32_t)tid < a.nblk ? (uint64_t)a.bmax[bo] << 32 : 0;
+  const float bev = (uint32_t)tid < a.nblk ? a.bexp[bo] : 0.f;
   uint64_t key[kRowTiles];
-  float tsv[kRowTiles];
 #pragma unroll
   for (int i = 0; i < kRowTiles; ++i) {
     const uint32_t t = tid + i * kRowThreads;
-    key[i] = t < NT ? tk[sidx(t)] : 0;
-    tsv[i] = t < NT ? ts[sidx(t)] : 0.f;
+    // Equal tile maxima: the tile of the lower tokens first.
+    key[i] = t < NT ? ((uint64_t)tk[sidx(t)] << 32) | (0xFFFFFFFFu - t) : 0;
   }
   // High key words of this thread's tiles (absent tiles hold key 0, below
   // every real one, so they only count for the minimum when skipped).
@@ -467,9 +659,9 @@ __global__ __launch_bounds__(kRowThreads) void k_head_rows(const HeadArgs a) {
     hmax = max(hmax, hw);
     hmin = min(hmin, key[i] ? hw : 0xFFFFFFFFu);
   }
-  // 1. Log-sum-exp over the tiles.  The largest logit is the largest high
-  // key word; the tile terms use the hardware exponential (the tile sums do
-  // too; relative error about an ulp per term).
+  // 1. Log-sum-exp over the logits blocks.  The largest logit is the largest
+  // high key word; the block terms use the hardware exponential (the block
+  // sums do too; relative error about an ulp per term).
   hmax = wave_max_u32(hmax);
   hmin = ~wave_max_u32(~hmin);
   uint32_t bhmax = wave_max_u32((uint32_t)(bmv >> 32));
@@ -490,16 +682,10 @@ __global__ __launch_bounds__(kRowThreads) void k_head_rows(const HeadArgs a) {
     bhmin = min(bhmin, s_bwmin[w]);
   }
   const float M = key2f(hmax);
-  // Each wave's part of S = sum over tiles of tsum * exp(tile max - M); the
+  // Each wave's part of S = sum over blocks of bexp * exp(block max - M); the
   // parts are added up after a later barrier (step 3).
   {
-    float part = 0.f;
-#pragma unroll
-    for (int i = 0; i < kRowTiles; ++i) {
-      const uint32_t t = tid + i * kRowThreads;
-      if (t < NT) part += tsv[i] * __expf(key2f((uint32_t)(key[i] >> 32)) - M);
-    }
-    part = wave_add(part);
+    const float part = wave_add(bmv ? bev * __expf(key2f((uint32_t)(bmv >> 32)) - M) : 0.f);
     if (lane == 0) s_red[wave] = part;
   }
 
@@ -634,7 +820,7 @@ __global__ __launch_bounds__(kRowThreads) void k_head_rows(const HeadArgs a) {
     // cannot make the block write past it.
     list_tiles<kRowTiles, kRowThreads>(key, NT, mask, prefix, s_tiles, &s_ntile);
     // (With all tiles taken, every logit is a candidate.)
-    tau = take == NT ? 0 : (common | prefix);
+    tau = take == NT ? 0 : (common | prefix) & ~0xFFFFFFFFull;
     __syncthreads();
   }
   const uint32_t ntile = min(s_ntile, (uint32_t)kHeadMaxK);
@@ -711,7 +897,7 @@ __global__ __launch_bounds__(kRowThreads) void k_head_rows(const HeadArgs a) {
 // at B = 64) so that the second can select from them, and read back about 2%
 // of them.  Here each wave keeps the logits of its tile groups (at most two)
 // in registers, and two grid barriers take the place of that write:
-//   A. the logits as in k_head_logits (one block per compute unit, the same
+//   A. the logits (one block per compute unit, its waves claiming groups of
 //      tiles; claiming the second tile groups device-wide instead, first
 //      come first served, made the call slower, 93.2 against 73.4 us: the
 //      compute units that finish early take too many); after each tile
@@ -778,6 +964,11 @@ __device__ __forceinline__ uint64_t call_epoch(const HeadArgs& a) {
   return n / a.nblk;
 }
 
+// The number of the call with one-launch epoch e among the head's calls.
+__device__ __forceinline__ unsigned long long call_number(const HeadArgs& a, uint64_t e) {
+  return __hip_atomic_load(a.ncall, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + e + 1ull;
+}
+
 __device__ __forceinline__ void leave_call(const HeadArgs& a) {
   if (threadIdx.x == 0)
     (void)__hip_atomic_fetch_add(a.ectl + 16 * (blockIdx.x % kLeaveCtrs), 1ull, __ATOMIC_RELAXED,
@@ -822,7 +1013,7 @@ __device__ __forceinline__ void grid_barrier(const HeadArgs& a, uint64_t epoch, 
       const unsigned long long* f = flag + kBarLine * grp;
       for (uint32_t n = 0; ld_agent(f) < phase; ++n) {
         if (n == a.wait_limit) {
-          atomicMax(a.fault, (unsigned long long)epoch + 1ull);
+          atomicMax(a.fault, call_number(a, epoch));
           break;
         }
         __builtin_amdgcn_s_sleep(1);
@@ -1127,7 +1318,7 @@ __global__ __launch_bounds__(kFuseThreads) void k_head_fused(const HeadArgs a) {
 
   // D. Row b.
   const uint32_t row = b;
-  if (ld_agent((const unsigned long long*)a.fault) == (unsigned long long)ep + 1ull) {
+  if (ld_agent((const unsigned long long*)a.fault) == call_number(a, ep)) {
     for (uint32_t i = tid; i < K; i += kFuseThreads) {
       a.top_ids[(size_t)row * K + i] = -1;
       a.top_prob[(size_t)row * K + i] = 0.f;
@@ -1289,16 +1480,23 @@ __global__ __launch_bounds__(kFuseThreads) void k_head_fused(const HeadArgs a) {
 bool head_dim_supported(int D) { return D == 256 || D == 512 || D == 1024; }
 
 uint32_t head_lds_bytes(int D) {
-  return (uint32_t)(kCols * (D + 8) * 2 + kLogitWaves * 16 * 72 * 2 + 8 + kCols * 8);
+  // The one-launch kernel's staged rows and W tiles; the logits kernel's
+  // chunks and statistics for 256 rows.
+  return std::max<uint32_t>(kCols * (D + 8) * 2 + kLogitWaves * 16 * 72 * 2 + 8 + kCols * 8,
+                            2 * 256 * kChunk * 2 + kLogitWaves * (256 * 32 + 16 * kChunk * 2));
 }
 
+// Columns per block: as many 64-row groups as divide the rows evenly, at most
+// four (256 rows; the accumulators of a wave take half its registers).
 hipError_t launch_head_logits(const HeadArgs& a, hipStream_t s) {
-  const dim3 grid(a.nblk, (a.B + kCols - 1) / kCols);
-  switch (a.D) {
-    case 256: hipLaunchKernelGGL(k_head_logits<8>, grid, dim3(kLogitWaves * 64), 0, s, a); break;
-    case 512: hipLaunchKernelGGL(k_head_logits<16>, grid, dim3(kLogitWaves * 64), 0, s, a); break;
-    case 1024: hipLaunchKernelGGL(k_head_logits<32>, grid, dim3(kLogitWaves * 64), 0, s, a); break;
-    default: return hipErrorInvalidValue;
+  if (!head_dim_supported((int)a.D) || a.nblk > (uint32_t)kRowThreads) return hipErrorInvalidValue;
+  const uint32_t groups = (a.B + 63) / 64, ny = (groups + 3) / 4;
+  const dim3 grid(a.nblk, ny), block(kLogitWaves * 64);
+  switch ((groups + ny - 1) / ny) {
+    case 1: hipLaunchKernelGGL((k_head_logits<4, 3, 2>), grid, block, 0, s, a); break;
+    case 2: hipLaunchKernelGGL((k_head_logits<8, 3, 2>), grid, block, 0, s, a); break;
+    case 3: hipLaunchKernelGGL((k_head_logits<12, 2, 2>), grid, block, 0, s, a); break;
+    default: hipLaunchKernelGGL((k_head_logits<16, 2, 2>), grid, block, 0, s, a); break;
   }
   return hipGetLastError();
 }
@@ -1322,6 +1520,8 @@ bool head_fused_fits(const HeadArgs& a) {
   const uint32_t tiles = ((a.V + 15) / 16 + a.nblk - 1) / a.nblk;
   return (tiles + kTileGroup - 1) / kTileGroup <= (uint32_t)(kFuseGroups * kLogitWaves);
 }
+
+bool head_fused_faster(const HeadArgs& a) { return a.B > 16 && a.V >= (1u << 17); }
 
 bool head_fused_resident(int D) {
   const void* f = D == 256 ? (const void*)k_head_fused<8>

@@ -16,13 +16,13 @@ struct tfe_head {
   const void* w = nullptr;   // caller's [V x D] bf16 projection (not owned)
   uint32_t V = 0, D = 0, max_batch = 0, max_k = 0;
   // Scratch, rows = max_batch rounded up to 64 (the logits kernel writes
-  // whole 64-row groups), tiles = V rounded up to 32 (whole 32-token
+  // whole 16-row tiles), tiles = V rounded up to 32 (whole 32-token
   // super-tiles), over 16.
   float* d_logits = nullptr;  // [rows x tiles x 16]
-  uint64_t* d_tkey = nullptr; // [rows x tiles rounded up to 16]
-  float* d_tsum = nullptr;    // [rows x tiles rounded up to 16]
-  uint64_t* d_bmax = nullptr; // [rows x compute units]
-  // Scratch of the one-launch path (calls of at most 64 rows, also under
+  uint32_t* d_tkey = nullptr; // [rows x tiles rounded up to 32]
+  uint32_t* d_bmax = nullptr; // [rows x compute units]
+  float* d_bexp = nullptr;    // [rows x compute units]
+  // Scratch of the one-launch path (some calls of at most 64 rows, also under
   // capture, when the device can launch it): barrier counters, call epoch and fault word,
   // per (row, block) maxima, sums and candidate counts, then the candidate
   // segments (ccap keys per row and block).
@@ -33,6 +33,7 @@ struct tfe_head {
   // head waits for it (and for nothing else on the device).
   hipEvent_t ev_last = nullptr;
   bool recorded = false;
+  hipStream_t last_stream = nullptr;  // of that call
 };
 
 namespace tfe {
@@ -57,7 +58,7 @@ void release(tfe_head* h) {
   (void)hipSetDevice(h->device);
   if (h->recorded) (void)hipEventSynchronize(h->ev_last);
   forget_fused(h);
-  void* bufs[] = {h->d_logits, h->d_tkey, h->d_tsum, h->d_bmax, h->d_fuse};
+  void* bufs[] = {h->d_logits, h->d_tkey, h->d_bmax, h->d_bexp, h->d_fuse};
   for (void* b : bufs) dev_free(b);
   if (h->ev_last) (void)hipEventDestroy(h->ev_last);
   (void)hipSetDevice(cur);
@@ -66,44 +67,53 @@ void release(tfe_head* h) {
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
-// One-launch calls of all heads on a device run one after another: a call
-// on another stream than the previous one waits on the device for that
-// call's event (the head's ev_last, recorded right after each call).  Two of
-// them side by side could each hold part of the compute units with blocks
-// waiting at a grid barrier for blocks of their own that cannot start.
-// Calls on the stream of the previous one are ordered by the stream itself
-// and add nothing.  The stream handle is only compared, never used.
+// Calls of one head share its scratch and run one after another: a call on
+// another stream than the previous one waits on the device for that call's
+// event (ev_last, recorded right after each call).  One-launch calls of all
+// heads on a device do so too: two of them side by side could each hold part
+// of the compute units with blocks waiting at a grid barrier for blocks of
+// their own that cannot start.  Calls on the stream of the previous one are
+// ordered by the stream itself and add nothing.  The stream handles are only
+// compared, never used.
 constexpr int kOrderDevices = 64;
-std::mutex g_fused_mu;
+std::mutex g_order_mu;
 const tfe_head* g_fused_head[kOrderDevices];
 hipStream_t g_fused_stream[kOrderDevices];
 
 // A head that is released stops being the previous call's head (release
 // has waited for its last call).
 void forget_fused(const tfe_head* h) {
-  std::lock_guard<std::mutex> lock(g_fused_mu);
+  std::lock_guard<std::mutex> lock(g_order_mu);
   if (h->device >= 0 && h->device < kOrderDevices && g_fused_head[h->device] == h)
     g_fused_head[h->device] = nullptr;
 }
 
-// Enqueues launch() on `stream` behind the previous one-launch call on the
-// device, then records h->ev_last behind it.
+// Enqueues launch() on `stream` behind the head's previous call (a one-launch
+// call: and behind the device's previous one), then records h->ev_last
+// behind it.
 template <class F>
-tfe_status fused_in_order(tfe_head* h, hipStream_t stream, F launch) {
-  std::lock_guard<std::mutex> lock(g_fused_mu);
-  const tfe_head* prev = g_fused_head[h->device];
-  if (prev && g_fused_stream[h->device] != stream)
-    HEAD_HIP(hipStreamWaitEvent(stream, prev->ev_last, 0), "head ordering wait");
+tfe_status in_order(tfe_head* h, hipStream_t stream, bool one_launch, F launch) {
+  std::lock_guard<std::mutex> lock(g_order_mu);
+  if (h->recorded && h->last_stream != stream)
+    HEAD_HIP(hipStreamWaitEvent(stream, h->ev_last, 0), "head ordering wait");
+  if (one_launch) {
+    const tfe_head* prev = g_fused_head[h->device];
+    if (prev && prev != h && g_fused_stream[h->device] != stream)
+      HEAD_HIP(hipStreamWaitEvent(stream, prev->ev_last, 0), "head ordering wait");
+  }
   HEAD_HIP(launch(), "head launch");
   HEAD_HIP(hipEventRecord(h->ev_last, stream), "record");
   h->recorded = true;
-  g_fused_head[h->device] = h;
-  g_fused_stream[h->device] = stream;
+  h->last_stream = stream;
+  if (one_launch) {
+    g_fused_head[h->device] = h;
+    g_fused_stream[h->device] = stream;
+  }
   return TFE_OK;
 }
 
 // Layout of the one-launch scratch for nblk blocks: 8 KB of barrier
-// counters and flags (one 128-byte line each) and the fault word, two
+// counters and flags (one 128-byte line each), the call count and the fault word, two
 // [64 x nblk] word arrays, then the candidate segments.
 constexpr size_t kFuseCtl = 8192;
 size_t fuse_words(uint32_t nblk) { return (size_t)64 * nblk; }
@@ -117,6 +127,7 @@ void fuse_args(const tfe_head* h, HeadArgs* a) {
   a->bar = (unsigned long long*)p;
   a->ectl = (unsigned long long*)(p + 4352);  // 16 lines after the barrier's 33
   a->fault = (unsigned long long*)(p + kFuseCtl - 128);
+  a->ncall = (unsigned long long*)(p + kFuseCtl - 256);
   a->bhi = (uint32_t*)(p + kFuseCtl);
   a->bsum = a->bhi + n;
   a->cand = (uint64_t*)(p + fuse_cand_at((uint32_t)h->cus));
@@ -170,11 +181,11 @@ tfe_status create(const void* w, int32_t vocab, int32_t dim, int32_t max_batch, 
     h->max_batch = (uint32_t)max_batch;
     h->max_k = (uint32_t)max_k;
     const size_t nb = ((size_t)h->max_batch + 63) / 64 * 64, nt = (h->V + 31) / 32 * 2;
-    const size_t nt16 = (nt + 15) / 16 * 16;
+    const size_t nt32 = (nt + 31) / 32 * 32;
     if (dev_malloc((void**)&h->d_logits, nb * nt * 16 * sizeof(float)) != hipSuccess ||
-        dev_malloc((void**)&h->d_tkey, nb * nt16 * sizeof(uint64_t)) != hipSuccess ||
-        dev_malloc((void**)&h->d_tsum, nb * nt16 * sizeof(float)) != hipSuccess ||
-        dev_malloc((void**)&h->d_bmax, nb * (size_t)h->cus * sizeof(uint64_t)) != hipSuccess) {
+        dev_malloc((void**)&h->d_tkey, nb * nt32 * sizeof(uint32_t)) != hipSuccess ||
+        dev_malloc((void**)&h->d_bmax, nb * (size_t)h->cus * sizeof(uint32_t)) != hipSuccess ||
+        dev_malloc((void**)&h->d_bexp, nb * (size_t)h->cus * sizeof(float)) != hipSuccess) {
       st = fail(TFE_ERR_OOM, "head scratch for %u rows", h->max_batch);
       break;
     }
@@ -231,38 +242,36 @@ tfe_status topk(tfe_head* h, const void* hidden, int32_t B, int32_t K, int32_t* 
   a.hidden = hidden;
   a.logits = h->d_logits;
   a.tkey = h->d_tkey;
-  a.tsum = h->d_tsum;
   a.bmax = h->d_bmax;
+  a.bexp = h->d_bexp;
   a.top_ids = ids;
   a.top_prob = prob;
   a.V = h->V;
   a.tpitch = (h->V + 31) / 32 * 2;
-  a.tblocks = (a.tpitch + 15) / 16;
+  a.tblocks = (a.tpitch + 31) / 32;
   a.D = h->D;
   a.B = (uint32_t)B;
   a.K = (uint32_t)K;
   a.nblk = (uint32_t)h->cus;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   HEAD_HIP(hipStreamIsCapturing(stream, &cs), "hipStreamIsCapturing");
-  if (h->fused && head_fused_fits(a) && h->device < kOrderDevices) {
-    fuse_args(h, &a);
-    a.wait_limit = kHeadWaitLimit;
-    if (const char* wl = getenv("TFE_HEAD_WAIT_LIMIT")) a.wait_limit = (uint32_t)strtoul(wl, nullptr, 0);
-    // Captured: the graph's edges order the call (the call epoch is kept on
-    // the device, so replays stay aligned).
-    if (cs != hipStreamCaptureStatusNone) {
-      HEAD_HIP(launch_head_fused(a, stream), "head launch");
-      return TFE_OK;
-    }
-    return fused_in_order(h, stream, [&] { return launch_head_fused(a, stream); });
+  if (h->fused) fuse_args(h, &a);
+  const char* wl = getenv("TFE_HEAD_WAIT_LIMIT");
+  const bool one = h->fused && h->device < kOrderDevices && head_fused_fits(a) &&
+                   (wl || head_fused_faster(a));
+  a.wait_limit = wl ? (uint32_t)strtoul(wl, nullptr, 0) : kHeadWaitLimit;
+  auto launch = [&] {
+    if (one) return launch_head_fused(a, stream);
+    const hipError_t e = launch_head_logits(a, stream);
+    return e == hipSuccess ? launch_head_rows(a, stream) : e;
+  };
+  // Captured: the graph's edges order the call (the call counts are kept on
+  // the device, so replays stay aligned).
+  if (cs != hipStreamCaptureStatusNone) {
+    HEAD_HIP(launch(), "head launch");
+    return TFE_OK;
   }
-  HEAD_HIP(launch_head_logits(a, stream), "head logits launch");
-  HEAD_HIP(launch_head_rows(a, stream), "head top-K launch");
-  if (cs == hipStreamCaptureStatusNone) {
-    HEAD_HIP(hipEventRecord(h->ev_last, stream), "record");
-    h->recorded = true;
-  }
-  return TFE_OK;
+  return in_order(h, stream, one, launch);
 }
 
 tfe_status last_fault(tfe_head* h, int64_t* call) {
@@ -275,8 +284,7 @@ tfe_status last_fault(tfe_head* h, int64_t* call) {
     return fail(TFE_ERR_INVALID_ARG, "head lives on device %d but device %d is current",
                 h->device, cur);
   if (h->recorded) HEAD_HIP(hipEventSynchronize(h->ev_last), "head wait");
-  // The fault word holds the largest (epoch + 1) of the calls that gave up:
-  // the 1-based number of the latest such call.
+  // The fault word holds the largest number of the calls that gave up.
   unsigned long long f = 0;
   HEAD_HIP(hipMemcpy(&f, h->d_fuse + kFuseCtl - 128, sizeof f, hipMemcpyDeviceToHost),
            "head fault word");

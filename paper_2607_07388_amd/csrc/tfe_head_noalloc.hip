@@ -1,13 +1,10 @@
 // Early-exit head top-K without any allocation, for callers that cannot
 // allocate device memory (code under HIP graph capture, serving loops,
 // harnesses that forbid hipMalloc).  The two-launch kernels of
-// tfe_head_topk (the same ids as its one-launch path, probabilities within
-// float32 rounding); their scratch (logits, tile statistics and block maxima
-// of one 64-row group, for vocabularies up to 2^18 and up to kNaMaxBlocks
+// tfe_head_topk; their scratch (logits, tile keys, block maxima and sums of
+// one 64-row group, for vocabularies up to 2^18 and up to kNaMaxBlocks
 // compute units) is a file-scope device array that each GPU holds until the
-// process ends.  (The one-launch path is not used here: its barrier targets
-// come from a per-call count kept on the host, which a captured graph would
-// replay unchanged.)
+// process ends.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -23,11 +20,11 @@ namespace {
 constexpr uint32_t kNaRows = 64;              // rows per call: one 64-row group
 constexpr uint32_t kNaTiles = kHeadMaxTiles;  // 16-token tiles of a 2^18 vocabulary
 constexpr size_t kNaLogitBytes = (size_t)kNaRows * kNaTiles * 16 * sizeof(float);  // 64 MiB
-constexpr size_t kNaKeyBytes = (size_t)kNaRows * kNaTiles * sizeof(uint64_t);      // 8 MiB
-constexpr size_t kNaSumBytes = (size_t)kNaRows * kNaTiles * sizeof(float);         // 4 MiB
+constexpr size_t kNaKeyBytes = (size_t)kNaRows * kNaTiles * sizeof(uint32_t);      // 4 MiB
 constexpr uint32_t kNaMaxBlocks = 1024;       // logits blocks: one per compute unit
-constexpr size_t kNaBmaxBytes = (size_t)kNaRows * kNaMaxBlocks * sizeof(uint64_t); // 512 KiB
-constexpr size_t kNaBytes = kNaLogitBytes + kNaKeyBytes + kNaSumBytes + kNaBmaxBytes;
+constexpr size_t kNaBmaxBytes = (size_t)kNaRows * kNaMaxBlocks * sizeof(uint32_t); // 256 KiB
+constexpr size_t kNaBexpBytes = (size_t)kNaRows * kNaMaxBlocks * sizeof(float);    // 256 KiB
+constexpr size_t kNaBytes = kNaLogitBytes + kNaKeyBytes + kNaBmaxBytes + kNaBexpBytes;
 constexpr int kNaMaxDevices = 64;
 
 }  // namespace
@@ -113,21 +110,21 @@ tfe_status topk_noalloc(const void* w, int32_t vocab, int32_t dim, const void* h
   a.w = w;
   a.hidden = hidden;
   a.logits = (float*)d.ptr;
-  a.tkey = (uint64_t*)(d.ptr + kNaLogitBytes);
-  a.tsum = (float*)(d.ptr + kNaLogitBytes + kNaKeyBytes);
-  a.bmax = (uint64_t*)(d.ptr + kNaLogitBytes + kNaKeyBytes + kNaSumBytes);
+  a.tkey = (uint32_t*)(d.ptr + kNaLogitBytes);
+  a.bmax = (uint32_t*)(d.ptr + kNaLogitBytes + kNaKeyBytes);
+  a.bexp = (float*)(d.ptr + kNaLogitBytes + kNaKeyBytes + kNaBmaxBytes);
   a.top_ids = ids;
   a.top_prob = prob;
   a.V = (uint32_t)vocab;
   a.tpitch = (a.V + 31) / 32 * 2;
-  a.tblocks = (a.tpitch + 15) / 16;
+  a.tblocks = (a.tpitch + 31) / 32;
   a.D = (uint32_t)dim;
   a.B = (uint32_t)B;
   a.K = (uint32_t)K;
   a.nblk = (uint32_t)d.cus;
-  // One 64-row group: logits [tpitch x 64 x 16] <= kNaLogitBytes, statistics
-  // [tblocks x 64 x 16] <= kNaKeyBytes / 8 entries, block maxima
-  // [nblk x 64] <= kNaBmaxBytes / 8.
+  // One 64-row group: logits [tpitch x 64 x 16] <= kNaLogitBytes, tile keys
+  // [tblocks x 64 x 32] <= kNaKeyBytes / 4, block maxima and sums
+  // [nblk x 64] <= kNaBmaxBytes / 4 and kNaBexpBytes / 4.
   e = launch_head_logits(a, stream);
   if (e == hipSuccess) e = launch_head_rows(a, stream);
   if (e != hipSuccess) return fail(TFE_ERR_HIP, "head launch: %s", hipGetErrorString(e));

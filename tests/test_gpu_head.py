@@ -77,6 +77,34 @@ def test_integer_logits_bit_exact_ids(V, D, B, K):
     head.close()
 
 
+@pytest.mark.parametrize("V,D,B,K", [
+    (37 * 16 + 1, 256, 65, 40),   # fewer tiles than blocks; one row in the second 64-row group
+    (9000, 256, 129, 33),         # three groups; two or three tiles per block
+    (33333, 512, 192, 64),        # three whole groups, ragged vocabulary
+    (66000, 256, 250, 256),       # four groups, one full round of tiles and a rest
+    (151936, 256, 256, 16),       # four whole groups, the backbone vocabulary
+    (20011, 1024, 257, 50),       # two blocks of columns, the second with spare groups
+    (200, 256, 300, 200),         # every token, most blocks without tiles
+])
+def test_wide_batches_bit_exact_ids(V, D, B, K):
+    """Calls of more than 64 rows: every column shape of the logits kernel at
+    ragged rows and tokens.  Integer logits (below 2^24) are exact, so ids
+    match bit for bit; probabilities as above."""
+    w, h = int_inputs(V + D + B, V, D, B)
+    head = Head(w, B, K)
+    ids, prob = head.topk(h, K)
+    rows = np.unique(np.array([0, 1, 63, 64, 65, 127, 128, 191, 192, B // 2, B - 2, B - 1]))
+    rows = rows[rows < B]
+    eids, eprob = oracle.head_topk(w, h[rows], K, synth.BF16)
+    np.testing.assert_array_equal(ids[rows], eids)
+    np.testing.assert_allclose(prob[rows], eprob, rtol=1e-5, atol=1e-36)
+    # Rows do not depend on their place in the batch.
+    ids2, prob2 = head.topk(np.roll(h, 1, axis=0), K)
+    np.testing.assert_array_equal(np.roll(ids2, -1, axis=0), ids)
+    np.testing.assert_allclose(np.roll(prob2, -1, axis=0), prob, rtol=2e-6, atol=1e-36)
+    head.close()
+
+
 def test_integer_logits_with_many_ties():
     """Entries in {0, 1}: logits take few distinct values, so the K-th place
     falls inside a large group of equal logits resolved by token id."""
