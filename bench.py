@@ -846,7 +846,8 @@ def run_head(args):
 
 
 def build_bytes_per_window(n, vocab):
-    """Data the construction pipeline moves per window of the stream.  A key
+    """Data a construction that sorts every window moves per window (what
+    `sort_gbps` prices; tfe_ngram_top sorts only the selected n-grams).  A key
     holds 18 n bits (one more when vocab = 2^18, whose invalid-window mark
     needs a bit above the token fields); the radix passes take 9 bits each.
     n <= 3: the first pass forms the keys from the tokens (4 B read by its
@@ -865,6 +866,14 @@ def build_bytes_per_window(n, vocab):
         return 16 + 24 * (passes - 1) + 16
     hi_passes = (18 + extra + 8) // 9
     return 20 + 5 * 32 + hi_passes * 28 + 24
+
+
+def construction_bytes_per_window(n):
+    """Data tfe_ngram_top moves per window of the stream: the tokens read by
+    the partition's histogram and by its scatter (4 B each), the remainder
+    word (4 B for n <= 2, else 8) written by the scatter and read by the
+    count.  The distinct n-grams are far fewer."""
+    return 8 + 2 * (4 if n <= 2 else 8)
 
 
 def run_build(args):
@@ -902,10 +911,11 @@ def run_build(args):
                 m = tfe.tfe_ngram_top(tok_d, N, synth.V, n, skip, top, tup, cnt,
                                       stream.cuda_stream)
             sec = (time.perf_counter() - t0) / reps
-            moved = N * build_bytes_per_window(n, synth.V)
+            moved = N * construction_bytes_per_window(n)
             runs.append({"stream": name, "n": n, "skip": skip, "top": top, "written": m,
                          "ms": sec * 1e3, "tokens_per_s": N / sec,
-                         "pipeline_gbps": moved / sec / 1e9})
+                         "pipeline_gbps": moved / sec / 1e9,
+                         "sort_gbps": N * build_bytes_per_window(n, synth.V) / sec / 1e9})
             print(json.dumps(runs[-1]), file=sys.stderr, flush=True)
         del tok_d
     main_run = runs[0]
@@ -926,7 +936,7 @@ def run_build(args):
                                "lengths and the 200M-token stream under 'runs'"},
         "roofline": {
             "bound": "hbm",
-            "kernel": "tfe_ngram_top pipeline (key formation, radix passes, run count)",
+            "kernel": "tfe_ngram_top pipeline (hash partition, LDS counts)",
             "achieved": main_run["pipeline_gbps"],
             "peak": HBM_PEAK_GBPS,
             "unit": "GB/s",

@@ -486,16 +486,37 @@ __device__ __forceinline__ uint64_t lane_of(uint64_t x, int l) {
 }
 
 // LDS table: 16384 entries of 32-bit remainders (128 KB) or 8192 of 64-bit
-// ones (96 KB).
+// ones (96 KB), in buckets of four that are read whole: at the loads of real
+// streams (up to 3/4) the slowest lane of a wave needs some 20 single entries
+// but 5 buckets.
 template <class K>
 constexpr uint32_t agg_slots() { return sizeof(K) == 4 ? 16384u : 8192u; }
 template <class K>
 struct Agg {
-  K key[agg_slots<K>()];
+  alignas(16) K key[agg_slots<K>()];
   uint32_t cnt[agg_slots<K>()];
   uint32_t over, out;
 };
-constexpr uint32_t kMaxProbe = 192;  // a longer probe gives the table up as full
+constexpr uint32_t kMaxProbe = 64;  // buckets; a longer probe gives the table up as full
+
+// The four keys of a bucket.  Each is read as it was at some moment; a key
+// never changes once it is set.
+__device__ __forceinline__ void read_bucket(const uint32_t* p, uint32_t* k) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  typedef const volatile __attribute__((address_space(3))) u32x4 lds_u32x4;
+  const u32x4 v = *(lds_u32x4*)p;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) k[q] = v[q];
+}
+__device__ __forceinline__ void read_bucket(const uint64_t* p, uint64_t* k) {
+  typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+  typedef const volatile __attribute__((address_space(3))) u64x2 lds_u64x2;
+  const u64x2 a = *(lds_u64x2*)p, b = *(lds_u64x2*)(p + 2);
+  k[0] = a[0];
+  k[1] = a[1];
+  k[2] = b[0];
+  k[3] = b[1];
+}
 
 // The remainders that a (re)try takes: those whose selection string (the 16
 // low hash bits, then the remainder's own bits from the lowest) starts with
@@ -521,48 +542,103 @@ __device__ __forceinline__ bool get_bit(const Part2& s, int i) {
   return i < 16 ? (s.vh >> i) & 1u : (s.vr >> (i - 16)) & 1ull;
 }
 
-// Adds w to the count of r, in the lanes with act.  ONE: w = 1 in every lane,
-// and the lanes that hold the first one's remainder add up first.
-template <class K, bool ONE>
+// One look at bucket s of the table for remainder r: true once w is added to
+// its count; otherwise s is where to look next.  A bucket's entries are taken
+// from its first one on, so a remainder is in the first bucket from its own
+// that had room for it, and in one entry: a lane that loses an entry to
+// another remainder reads the bucket again (at most four times: each time an
+// entry more is taken).
+template <class K>
+__device__ __forceinline__ bool agg_step(Agg<K>& L, uint32_t mask, K r, uint32_t w, uint32_t& s) {
+  const K none = (K)~(K)0;
+  K k[4];
+  read_bucket(&L.key[s], k);
+  int at = -1, room = -1;
+#pragma unroll
+  for (int q = 3; q >= 0; --q) {
+    at = k[q] == r ? q : at;
+    room = k[q] == none ? q : room;
+  }
+  if (at < 0 && room >= 0) {
+    K old = none;
+    if (__hip_atomic_compare_exchange_strong(&L.key[s + (uint32_t)room], &old, r, __ATOMIC_RELAXED,
+                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) ||
+        old == r)
+      at = room;
+  }
+  if (at >= 0) atomicAdd(&L.cnt[s + (uint32_t)at], w);
+  else if (room < 0) s = (s + 4) & mask;
+  return at >= 0;
+}
+constexpr uint32_t kMaxLooks = 5 * kMaxProbe;  // at most five at a bucket
+
+// Adds w to the count of r, in the lanes with act.
+template <class K>
 __device__ __forceinline__ void agg_add(Agg<K>& L, const Part2& sel, uint32_t mask, int hshift,
                                         K r, uint32_t w, bool act) {
   const uint32_t h = rem_hash(r);
-  act = act && taken(sel, h, r);
-  if (ONE) {
-    const uint64_t am = __builtin_amdgcn_ballot_w64(act);
-    if (!am) return;
-    const int f = __builtin_ctzll(am);
-    const uint64_t same = __builtin_amdgcn_ballot_w64(act && r == lane_of(r, f));
-    const int lane = threadIdx.x & 63;
-    if ((same >> lane) & 1ull) {
-      act = lane == f;
-      w = (uint32_t)__builtin_popcountll(same);
-    }
-  }
-  if (!act) return;
-  const K none = (K)~(K)0;
-  uint32_t s = (h >> hshift) & mask;
-  for (uint32_t n = 0; n < kMaxProbe; ++n) {
-    K k = __hip_atomic_load(&L.key[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    if (k == none) {
-      k = none;
-      if (__hip_atomic_compare_exchange_strong(&L.key[s], &k, r, __ATOMIC_RELAXED,
-                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))
-        k = r;
-    }
-    if (k == r) {
-      atomicAdd(&L.cnt[s], w);
-      return;
-    }
-    s = (s + 1) & mask;
-  }
+  if (!act || !taken(sel, h, r)) return;
+  uint32_t s = (h >> hshift) & mask & ~3u;
+  for (uint32_t n = 0; n < kMaxLooks; ++n)
+    if (agg_step(L, mask, r, w, s)) return;
   L.over = 1u;
 }
 
-// Counts the remainders that feed(add) passes to add(r, w, act) (called by
-// whole waves; at most len in all), and writes the distinct ones with their
-// counts to okey / ocnt.  Returns their number (block-uniform).
-template <class K, bool ONE, class Feed>
+// Counts r[u] once in the lanes with act bit u, U remainders per lane.  The
+// lanes of a wave that hold the first one's remainder add up first (heavily
+// repeated n-grams).  Each lane works through its own remainders, a look per
+// turn: waiting for the slowest lane at every remainder took 5 looks a
+// remainder, this way about 2.  Counting the 2-grams of 2^26 Zipf tokens took
+// 425 us with single entries, 386 with buckets and takes 332 with turns; the
+// 4-grams of 20M (4900 windows a partition, where starting a block weighs
+// more) 267, 234 and 230.
+template <class K, int U>
+__device__ __forceinline__ void agg_count_each(Agg<K>& L, const Part2& sel, uint32_t mask,
+                                               int hshift, K (&r)[U], uint32_t act) {
+  const int lane = threadIdx.x & 63;
+  uint32_t q[U];  // home bucket << 8 | weight
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const uint32_t h = rem_hash(r[u]);
+    const bool in = ((act >> u) & 1u) && taken(sel, h, r[u]);
+    uint32_t w = in ? 1u : 0u;
+    const uint64_t am = __builtin_amdgcn_ballot_w64(in);
+    if (am) {
+      const int f = __builtin_ctzll(am);
+      const uint64_t same = __builtin_amdgcn_ballot_w64(in && r[u] == lane_of(r[u], f));
+      if ((same >> lane) & 1ull) w = lane == f ? (uint32_t)__builtin_popcountll(same) : 0u;
+    }
+    q[u] = (((h >> hshift) & mask) >> 2 << 8) | w;
+  }
+  uint32_t s = q[0] >> 8 << 2, n = 0;
+  for (int left = U; left > 0;) {
+    const uint32_t w = q[0] & 255u;
+    bool next = w == 0;
+    if (!next) {
+      next = agg_step(L, mask, r[0], w, s);
+      if (!next && ++n == kMaxLooks) {
+        L.over = 1u;
+        next = true;
+      }
+    }
+    if (next) {
+      --left;
+      n = 0;
+#pragma unroll
+      for (int u = 0; u + 1 < U; ++u) {
+        r[u] = r[u + 1];
+        q[u] = q[u + 1];
+      }
+      s = q[0] >> 8 << 2;
+    }
+  }
+}
+
+// Counts the remainders that feed(count, full) has count(f) add (f is called
+// by whole waves with the table's parameters; at most len remainders in all;
+// full() is true once the table has overflowed), and writes the distinct ones
+// with their counts to okey / ocnt.  Returns their number (block-uniform).
+template <class K, class Feed>
 __device__ uint32_t agg_count(Agg<K>& L, uint32_t len, Feed feed, K* okey, uint32_t* ocnt,
                               uint64_t* fault) {
   const int tid = threadIdx.x, lane = tid & 63;
@@ -584,7 +660,7 @@ __device__ uint32_t agg_count(Agg<K>& L, uint32_t len, Feed feed, K* okey, uint3
     }
     if (tid == 0) L.over = 0u;
     __syncthreads();
-    feed([&](K r, uint32_t w, bool act) { agg_add<K, ONE>(L, sel, slots - 1, hshift, r, w, act); },
+    feed([&](auto f) { f(sel, slots - 1, hshift); },
          [&] { return *(volatile uint32_t*)&L.over != 0u; });
     __syncthreads();
     const bool over = L.over != 0u;
@@ -624,21 +700,24 @@ __global__ __launch_bounds__(1024) void k_count_slices(Plan a, const K* rem, uin
   const uint32_t beg = a.start[p] + (blockIdx.x - a.first[p]) * S;
   const uint32_t len = min(S, a.start[p + 1] - beg);
   const K* src = rem + beg;
-  auto feed = [&](auto add, auto full) {
+  auto feed = [&](auto count, auto full) {
     constexpr uint32_t U = 4;
     for (uint32_t b = 0; b < len; b += 1024 * U) {
       if (full()) break;
       K r[U];
+      uint32_t act = 0;
 #pragma unroll
       for (uint32_t u = 0; u < U; ++u) {
         const uint32_t i = b + u * 1024 + threadIdx.x;
         r[u] = src[i < len ? i : 0u];
+        act |= i < len ? 1u << u : 0u;
       }
-#pragma unroll
-      for (uint32_t u = 0; u < U; ++u) add(r[u], 1u, b + u * 1024 + threadIdx.x < len);
+      count([&](const Part2& sel, uint32_t mask, int hshift) {
+        agg_count_each<K, U>(L, sel, mask, hshift, r, act);
+      });
     }
   };
-  const uint32_t n = agg_count<K, true>(L, len, feed, ukey + beg, ucnt + beg, a.state + kStFault);
+  const uint32_t n = agg_count<K>(L, len, feed, ukey + beg, ucnt + beg, a.state + kStFault);
   if (threadIdx.x == 0) a.nslice[blockIdx.x] = n;
 }
 
@@ -654,18 +733,22 @@ __global__ __launch_bounds__(1024) void k_count_merge(Plan a, const K* ukey, con
     return;
   }
   const uint32_t len = a.start[p + 1] - beg;
-  auto feed = [&](auto add, auto full) {
+  auto feed = [&](auto count, auto full) {
     for (uint32_t j = 0; j < ns; ++j) {
       const uint32_t n = a.nslice[f + j], s = beg + j * S;
       for (uint32_t b = 0; b < n; b += 1024) {
         if (full()) return;
         const uint32_t i = b + threadIdx.x;
         const uint32_t q = s + (i < n ? i : 0u);
-        add(ukey[q], ucnt[q], i < n);
+        const K r = ukey[q];
+        const uint32_t w = ucnt[q];
+        count([&](const Part2& sel, uint32_t mask, int hshift) {
+          agg_add<K>(L, sel, mask, hshift, r, w, i < n);
+        });
       }
     }
   };
-  const uint32_t n = agg_count<K, false>(L, len, feed, mkey + beg, mcnt + beg, a.state + kStFault);
+  const uint32_t n = agg_count<K>(L, len, feed, mkey + beg, mcnt + beg, a.state + kStFault);
   if (threadIdx.x == 0) a.nuniq[p] = n;
 }
 
