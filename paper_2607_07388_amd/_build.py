@@ -1,11 +1,14 @@
-"""Build libtfe.so (HIP kernels for gfx950 + host runtime + C ABI) in-tree."""
+"""Build libtfe.so (HIP kernels for gfx950 + host runtime + C ABI) and _calls.so (the
+per-step calls of the Python binding) in-tree."""
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 ROOT = os.path.dirname(HERE)
 SO = os.path.join(HERE, "libtfe.so")
+CALLS = os.path.join(HERE, "_calls.so")
 ROCM_INC = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include")
 
 SOURCES = ["tfe_api.cpp", "tfe_head_api.cpp", "tfe_host.cpp", "tfe_stage.cpp", "tfe_build.hip", "tfe_head.hip",
@@ -17,7 +20,18 @@ HIP_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
              "-I", os.path.join(ROOT, "include")]
 
 
+def build_calls():
+    cmd = ["g++", "-O3", "-std=c++17", "-shared", "-fPIC", "-Wall", "-fvisibility=hidden",
+           "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "tfe_calls.cpp"),
+           "-o", CALLS + ".tmp"]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("_calls build failed: %s\n%s" % (" ".join(cmd), r.stdout))
+    os.replace(CALLS + ".tmp", CALLS)
+
+
 def build(verbose=False):
+    build_calls()
     objs = []
     for src in SOURCES:
         path = os.path.join(CSRC, src)

@@ -6,6 +6,11 @@ integer handle, None (the default stream) or a ``torch.cuda.Stream``.
 A negative status raises ``TfeError`` carrying ``tfe_last_error()``.
 There is no fallback: if the library cannot be built or loaded, importing
 fails.
+
+The calls a serving loop makes at every step (lookups, prefetches, head top-K)
+go through the native module ``_calls``, which takes the plain case and hands
+any other to the ctypes function of the same name here.  (A batch-64 decode
+lookup from Python, back to back: 7.6 us through ctypes, 6.3 so.)
 """
 import ctypes
 import os
@@ -82,6 +87,8 @@ def share_torch_hip_runtime():
 def _load():
     if not os.path.exists(_build.SO):
         _build.build()
+    elif not os.path.exists(_build.CALLS):
+        _build.build_calls()
     share_torch_hip_runtime()
     L = ctypes.CDLL(_build.SO)
     if len(hip_runtimes()) > 1:
@@ -297,3 +304,20 @@ def make_desc(phrase_tokens, phrase_len, n_min, n_max, vocab, values, dim, dtype
     d.pinned_rows = pinned_rows
     d.pageable_values = addr(pageable_values)
     return d
+
+
+# The per-step calls: native from here on, with the functions above for any
+# form of arguments that is not the plain one.
+_BY_CTYPES = {f.__name__: f for f in (tfe_lookup_inject, tfe_lookup_inject_multi, tfe_prefetch,
+                                      tfe_prefetch_scored, tfe_head_topk)}
+
+
+def _bind_calls():
+    from . import _calls
+    _calls.bind(_check, {n: (f, ctypes.cast(getattr(lib, n), ctypes.c_void_p).value)
+                         for n, f in _BY_CTYPES.items()})
+    for n in _BY_CTYPES:
+        globals()[n] = getattr(_calls, n)
+
+
+_bind_calls()
