@@ -354,7 +354,8 @@ tfe_status tfe_head_topk_noalloc(const void *w_pref, int32_t vocab, int32_t dim,
  *   written     HOST: number of ranks written (fewer than top when the
  *               stream has fewer than skip + top distinct tuples)
  * Synchronous: returns once the outputs are complete.  Its scratch (device
- * memory of the current device: about 20 bytes per token, 40 for 4-grams)
+ * memory of the current device: about 17 bytes per token, 26 for 3- and
+ * 4-grams, and 18 or 34 per n-gram ranked)
  * stays with the library after the call and is reused by later calls of a
  * similar size, until tfe_ngram_release; a call that finds no fitting idle
  * buffer first returns the idle ones.  Safe to call from several host
