@@ -770,6 +770,23 @@ struct Uniq {
 
 // ---- 3. selection -----------------------------------------------------------
 
+// The walks over the distinct n-grams wait for memory, not for its bandwidth:
+// a thread requests kWalk counts together (0 past the last).  The histogram and
+// the records of the 2-grams of 2^26 tokens took 33 and 62 us one at a time,
+// 28 and 56 so; of the 4-grams of 20M 32 and 71, 25 and 62.
+constexpr uint32_t kWalk = 6;
+__device__ __forceinline__ void load_counts(const uint32_t* c, uint32_t n, uint32_t b,
+                                            uint32_t (&v)[kWalk]) {
+#pragma unroll
+  for (uint32_t q = 0; q < kWalk; ++q) {
+    const uint32_t i = b + q * 1024 + threadIdx.x;
+    v[q] = c[min(i, n - 1)];
+  }
+#pragma unroll
+  for (uint32_t q = 0; q < kWalk; ++q)
+    if (b + q * 1024 + threadIdx.x >= n) v[q] = 0u;
+}
+
 // Histogram of min(count, kSelBins - 1).  Most counts are small, so the
 // lanes holding the first lane's bin add their number with one atomic.
 template <class K>
@@ -782,16 +799,20 @@ __global__ __launch_bounds__(1024) void k_sel_hist(Uniq<K> u) {
     const K* k;
     const uint32_t* c;
     const uint32_t n = u.at(p, &k, &c);
-    for (uint32_t b = 0; b < n; b += 1024) {
-      const uint32_t i = b + threadIdx.x;
-      const bool in = i < n;
-      const uint32_t bin = in ? min(c[i], (uint32_t)kSelBins - 1u) : 0u;
-      const uint32_t b0 = __builtin_amdgcn_readfirstlane(bin);
-      const uint64_t m = __builtin_amdgcn_ballot_w64(in && bin == b0);
-      if (in && bin != b0)
-        atomicAdd(&h[bin], 1u);
-      else if (in && (m & lt) == 0)
-        atomicAdd(&h[b0], (uint32_t)__builtin_popcountll(m));
+    for (uint32_t b = 0; b < n; b += 1024 * kWalk) {
+      uint32_t v[kWalk];
+      load_counts(c, n, b, v);
+#pragma unroll
+      for (uint32_t q = 0; q < kWalk; ++q) {
+        const bool in = b + q * 1024 + threadIdx.x < n;
+        const uint32_t bin = min(v[q], (uint32_t)kSelBins - 1u);
+        const uint32_t b0 = __builtin_amdgcn_readfirstlane(bin);
+        const uint64_t m = __builtin_amdgcn_ballot_w64(in && bin == b0);
+        if (in && bin != b0)
+          atomicAdd(&h[bin], 1u);
+        else if (in && (m & lt) == 0)
+          atomicAdd(&h[b0], (uint32_t)__builtin_popcountll(m));
+      }
     }
   }
   __syncthreads();
@@ -935,17 +956,21 @@ __global__ __launch_bounds__(1024) void k_gather(Uniq<Rem<NG>> u, int pbits, uin
       const Rem<NG>* k;
       const uint32_t* c;
       const uint32_t n = u.at(p, &k, &c);
-      for (uint32_t b = 0; b < n; b += 1024) {
-        const uint32_t i = b + threadIdx.x;
-        const uint32_t ci = i < n ? c[i] : 0u;
-        bool keep = ci >= cstar && ci != 0u;
-        uint32_t x[4] = {0u, 0u, 0u, 0u};
-        if (keep && tie && ci == cstar) {
-          join_window<NG>(p, k[i], pbits, x);
-          const uint64_t hi = key_hi(x);
-          keep = hi < th || (hi == th && key_lo(x) <= tl);
+      for (uint32_t b = 0; b < n; b += 1024 * kWalk) {
+        uint32_t v[kWalk];
+        load_counts(c, n, b, v);
+#pragma unroll
+        for (uint32_t q = 0; q < kWalk; ++q) {
+          const uint32_t i = b + q * 1024 + threadIdx.x, ci = v[q];
+          bool keep = ci >= cstar && ci != 0u;
+          uint32_t x[4] = {0u, 0u, 0u, 0u};
+          if (keep && tie && ci == cstar) {
+            join_window<NG>(p, k[i], pbits, x);
+            const uint64_t hi = key_hi(x);
+            keep = hi < th || (hi == th && key_lo(x) <= tl);
+          }
+          use(p, k, i, ci, keep);
         }
-        use(p, k, i, ci, keep);
       }
     }
   };
@@ -989,7 +1014,9 @@ constexpr uint32_t max_buckets() { return sizeof(R) == 8 ? 4096u : 2048u; }
 template <class R>
 constexpr uint64_t bucket_sort_max() { return 2048ull * max_buckets<R>(); }
 
-// Bitonic sort of a[0, N2) in LDS, ascending; N2 a power of two.
+// Bitonic sort of a[0, N2) in LDS, ascending; N2 a power of two.  (Block
+// barriers only where a step leaves a wave's 128 elements changed nothing in
+// the bucket sorts and took 4 of 41 us off the sample's.)
 template <class R>
 __device__ void lds_sort(R* a, uint32_t N2) {
   for (uint32_t size = 2; size <= N2; size <<= 1) {
