@@ -14,7 +14,8 @@
 //   2. each partition's remainders are counted in an LDS hash table by one
 //      block (slices of a partition that heavy repetition made long are
 //      counted by several blocks, whose partial counts a second launch adds
-//      up; a table that fills up is retried on halves of the remainders);
+//      up; a slice that fills the table is regrouped by hash into parts that
+//      do not);
 //   3. the (skip + top)-th largest count c* from a histogram of the counts;
 //   4. the n-grams with count >= c* become records that compare in rank
 //      order: count descending, then tuple (when far more n-grams have
@@ -495,10 +496,21 @@ template <class K>
 struct Agg {
   alignas(16) K key[agg_slots<K>()];
   uint32_t cnt[agg_slots<K>()];
-  uint32_t over, out;
+  uint32_t over;  // 0, or how much had been fed when the table was given up as full
+  uint32_t out;
 };
-constexpr uint32_t kMaxProbe = 64;  // buckets; a longer probe gives the table up as full
+// Looks; a remainder that needs more gives the table up as full, at about 17
+// of 20 entries taken (with steps of one bucket instead of the remainder's own,
+// at 14).  Every look beyond costs the wave: filling tables on to 19 of 20, with
+// 24 looks, took the 3-grams of 2^26 Zipf tokens from 2.96 to 3.24 ms a call;
+// asking at every look whether another wave has given up, the 2-grams from 1.04
+// to 1.06.
+constexpr uint32_t kMaxLooks = 14;
 
+// A word of LDS that other waves write meanwhile.
+__device__ __forceinline__ uint32_t read_word(const uint32_t* p) {
+  return *(const volatile __attribute__((address_space(3))) uint32_t*)p;
+}
 // The four keys of a bucket.  Each is read as it was at some moment; a key
 // never changes once it is set.
 __device__ __forceinline__ void read_bucket(const uint32_t* p, uint32_t* k) {
@@ -543,13 +555,15 @@ __device__ __forceinline__ bool get_bit(const Part2& s, int i) {
 }
 
 // One look at bucket s of the table for remainder r: true once w is added to
-// its count; otherwise s is where to look next.  A bucket's entries are taken
+// its count; otherwise s is where to look next (an odd number of buckets on,
+// which every remainder has of its own).  A bucket's entries are taken
 // from its first one on, so a remainder is in the first bucket from its own
 // that had room for it, and in one entry: a lane that loses an entry to
 // another remainder reads the bucket again (at most four times: each time an
 // entry more is taken).
 template <class K>
-__device__ __forceinline__ bool agg_step(Agg<K>& L, uint32_t mask, K r, uint32_t w, uint32_t& s) {
+__device__ __forceinline__ bool agg_step(Agg<K>& L, uint32_t mask, K r, uint32_t w, uint32_t step,
+                                         uint32_t& s) {
   const K none = (K)~(K)0;
   K k[4];
   read_bucket(&L.key[s], k);
@@ -567,21 +581,27 @@ __device__ __forceinline__ bool agg_step(Agg<K>& L, uint32_t mask, K r, uint32_t
       at = room;
   }
   if (at >= 0) atomicAdd(&L.cnt[s + (uint32_t)at], w);
-  else if (room < 0) s = (s + 4) & mask;
+  else if (room < 0) s = (s + step) & mask;
   return at >= 0;
 }
-constexpr uint32_t kMaxLooks = 5 * kMaxProbe;  // at most five at a bucket
+// Hash bits for the step: neither those of the home bucket nor the lowest,
+// which parts of a partition have in common.
+__device__ __forceinline__ uint32_t step_bits(uint32_t h) { return (h >> 6) & 0xFFFu; }
 
-// Adds w to the count of r, in the lanes with act.
+// Adds w to the count of r, in the lanes with act.  fed (> 0): how much the
+// feed has been through.
 template <class K>
 __device__ __forceinline__ void agg_add(Agg<K>& L, const Part2& sel, uint32_t mask, int hshift,
-                                        K r, uint32_t w, bool act) {
+                                        K r, uint32_t w, bool act, uint32_t fed) {
   const uint32_t h = rem_hash(r);
   if (!act || !taken(sel, h, r)) return;
-  uint32_t s = (h >> hshift) & mask & ~3u;
-  for (uint32_t n = 0; n < kMaxLooks; ++n)
-    if (agg_step(L, mask, r, w, s)) return;
-  L.over = 1u;
+  const uint32_t step = (step_bits(h) | 1u) << 2;
+  uint32_t s = (h >> hshift) & mask & ~3u, n = 0;
+  while (!agg_step(L, mask, r, w, step, s))
+    if (++n == kMaxLooks) {
+      L.over = fed;
+      return;
+    }
 }
 
 // Counts r[u] once in the lanes with act bit u, U remainders per lane.  The
@@ -594,9 +614,9 @@ __device__ __forceinline__ void agg_add(Agg<K>& L, const Part2& sel, uint32_t ma
 // more) 267, 234 and 230.
 template <class K, int U>
 __device__ __forceinline__ void agg_count_each(Agg<K>& L, const Part2& sel, uint32_t mask,
-                                               int hshift, K (&r)[U], uint32_t act) {
+                                               int hshift, K (&r)[U], uint32_t act, uint32_t fed) {
   const int lane = threadIdx.x & 63;
-  uint32_t q[U];  // home bucket << 8 | weight
+  uint32_t q[U];  // home bucket << 20 | step bits << 8 | weight
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const uint32_t h = rem_hash(r[u]);
@@ -608,16 +628,16 @@ __device__ __forceinline__ void agg_count_each(Agg<K>& L, const Part2& sel, uint
       const uint64_t same = __builtin_amdgcn_ballot_w64(in && r[u] == lane_of(r[u], f));
       if ((same >> lane) & 1ull) w = lane == f ? (uint32_t)__builtin_popcountll(same) : 0u;
     }
-    q[u] = (((h >> hshift) & mask) >> 2 << 8) | w;
+    q[u] = (((h >> hshift) & mask) >> 2 << 20) | (step_bits(h) << 8) | w;
   }
-  uint32_t s = q[0] >> 8 << 2, n = 0;
+  uint32_t s = q[0] >> 20 << 2, n = 0;
   for (int left = U; left > 0;) {
     const uint32_t w = q[0] & 255u;
     bool next = w == 0;
     if (!next) {
-      next = agg_step(L, mask, r[0], w, s);
+      next = agg_step(L, mask, r[0], w, ((q[0] >> 6) & 0x3FFCu) | 4u, s);
       if (!next && ++n == kMaxLooks) {
-        L.over = 1u;
+        L.over = fed;
         next = true;
       }
     }
@@ -629,96 +649,219 @@ __device__ __forceinline__ void agg_count_each(Agg<K>& L, const Part2& sel, uint
         r[u] = r[u + 1];
         q[u] = q[u + 1];
       }
-      s = q[0] >> 8 << 2;
+      s = q[0] >> 20 << 2;
     }
   }
 }
 
-// Counts the remainders that feed(count, full) has count(f) add (f is called
-// by whole waves with the table's parameters; at most len remainders in all;
-// full() is true once the table has overflowed), and writes the distinct ones
-// with their counts to okey / ocnt.  Returns their number (block-uniform).
-template <class K, class Feed>
-__device__ uint32_t agg_count(Agg<K>& L, uint32_t len, Feed feed, K* okey, uint32_t* ocnt,
-                              uint64_t* fault) {
-  const int tid = threadIdx.x, lane = tid & 63;
-  uint32_t slots = agg_slots<K>();
-  int hshift = sizeof(K) == 4 ? 18 : 19;
+// Entries that the table uses for at most len remainders.
+struct TableSize {
+  uint32_t slots;
+  int hshift;
+};
+template <class K>
+__device__ __forceinline__ TableSize agg_table(uint32_t len) {
+  TableSize t{agg_slots<K>(), sizeof(K) == 4 ? 18 : 19};
   static_assert(agg_slots<uint32_t>() == 1u << 14 && agg_slots<uint64_t>() == 1u << 13, "shift");
-  while (slots > 64 && slots / 2 >= 2 * (uint64_t)len) {
-    slots /= 2;
-    ++hshift;
+  while (t.slots > 64 && t.slots / 2 >= 2 * (uint64_t)len) {
+    t.slots /= 2;
+    ++t.hshift;
   }
-  const K none = (K)~(K)0;
+  return t;
+}
+
+// Counts, in a cleared table, the remainders that sel takes among those that
+// feed(count, full) has count(f) add (f is called by whole waves with the
+// table's parameters; full() is true once the table has overflowed).  Returns
+// 0, or how much had been fed when the table was given up (block-uniform).
+template <class K, class Feed>
+__device__ __forceinline__ uint32_t agg_walk(Agg<K>& L, const Part2& sel, const TableSize& t,
+                                             Feed feed) {
+  for (uint32_t e = threadIdx.x; e < t.slots; e += 1024) {
+    L.key[e] = (K)~(K)0;
+    L.cnt[e] = 0u;
+  }
+  if (threadIdx.x == 0) L.over = 0u;
+  __syncthreads();
+  feed([&](auto f) { f(sel, t.slots - 1, t.hshift); },
+       [&] { return read_word(&L.over) != 0u; });
+  __syncthreads();
+  const uint32_t over = L.over;
+  __syncthreads();  // over is read before it is cleared
+  return over;
+}
+
+// Appends the table's remainders and counts to okey / ocnt (L.out so far).
+template <class K>
+__device__ __forceinline__ void agg_emit(Agg<K>& L, const TableSize& t, K* okey, uint32_t* ocnt) {
+  const int lane = threadIdx.x & 63;
   const uint64_t lt = (1ull << lane) - 1ull;
-  if (tid == 0) L.out = 0u;
-  Part2 sel{0, 0u, 0ull};
-  for (;;) {
-    for (uint32_t e = tid; e < slots; e += 1024) {
-      L.key[e] = none;
-      L.cnt[e] = 0u;
+  for (uint32_t e = threadIdx.x; e < t.slots; e += 1024) {
+    const uint32_t c = L.cnt[e];
+    const uint64_t m = __builtin_amdgcn_ballot_w64(c != 0u);
+    uint32_t o = 0;
+    if (m && lane == 0) o = atomicAdd(&L.out, (uint32_t)__builtin_popcountll(m));
+    o = __builtin_amdgcn_readfirstlane(o) + (uint32_t)__builtin_popcountll(m & lt);
+    if (c != 0u) {
+      okey[o] = L.key[e];
+      ocnt[o] = c;
     }
-    if (tid == 0) L.over = 0u;
-    __syncthreads();
-    feed([&](auto f) { f(sel, slots - 1, hshift); },
-         [&] { return *(volatile uint32_t*)&L.over != 0u; });
-    __syncthreads();
-    const bool over = L.over != 0u;
-    if (over && sel.len < 16 + 63) {
-      __syncthreads();  // over is read before it is cleared
-      set_bit(sel, sel.len, false);
-      ++sel.len;
+  }
+  __syncthreads();
+}
+
+// Bits to select parts by after a table was given up at `over` of len fed: as
+// many as keep a part at 3/4 of the entries if the rest of the feed holds as
+// many distinct remainders.
+constexpr int kMaxSplit = 6;
+__device__ __forceinline__ int split_bits(uint32_t len, uint32_t over) {
+  int b = 1;
+  while (b < kMaxSplit && 7 * (uint64_t)len > (6 * (uint64_t)over) << b) ++b;
+  return b;
+}
+
+// Counts the remainders of root among those fed (at most len), in parts if
+// the table fills up, each of which walks the feed.
+template <class K, class Feed>
+__device__ __forceinline__ void agg_count(Agg<K>& L, const Part2& root, uint32_t len, Feed feed,
+                                          K* okey, uint32_t* ocnt, uint64_t* fault) {
+  const TableSize t = agg_table<K>(len);
+  Part2 sel = root;
+  int depth = root.len;  // bits that every part is selected by; more where one still overflows
+  for (;;) {
+    const uint32_t over = agg_walk(L, sel, t, feed);
+    if (over && sel.len < 16 + 63 - kMaxSplit) {
+      const bool first = sel.vh == root.vh && sel.vr == root.vr;
+      for (int b = sel.len == root.len ? split_bits(len, over) : 1; b > 0; --b)
+        set_bit(sel, sel.len++, false);
+      if (first) depth = sel.len;
       continue;
     }
-    if (over && tid == 0) *fault = 1ull;  // not reached: such a part holds one remainder
-    for (uint32_t e = tid; e < slots; e += 1024) {
-      const uint32_t c = L.cnt[e];
-      const uint64_t m = __builtin_amdgcn_ballot_w64(c != 0u);
-      uint32_t o = 0;
-      if (m && lane == 0) o = atomicAdd(&L.out, (uint32_t)__builtin_popcountll(m));
-      o = __builtin_amdgcn_readfirstlane(o) + (uint32_t)__builtin_popcountll(m & lt);
-      if (c != 0u) {
-        okey[o] = L.key[e];
-        ocnt[o] = c;
-      }
-    }
-    __syncthreads();
-    while (sel.len > 0 && get_bit(sel, sel.len - 1)) set_bit(sel, --sel.len, false);
-    if (sel.len == 0) break;
+    if (over && threadIdx.x == 0) *fault = 1ull;  // not reached: such a part holds one remainder
+    agg_emit(L, t, okey, ocnt);
+    while (sel.len > root.len && get_bit(sel, sel.len - 1)) set_bit(sel, --sel.len, false);
+    if (sel.len == root.len) break;
     set_bit(sel, sel.len - 1, true);
+    while (sel.len < depth) set_bit(sel, sel.len++, false);
   }
-  return L.out;
 }
 
-// One slice of a partition.
+// Adds the remainders of src[0, len), U of each thread at a time.
+template <class K, class Count, class Full>
+__device__ __forceinline__ void feed_rems(Agg<K>& L, const K* src, uint32_t len, Count count,
+                                          Full full) {
+  constexpr uint32_t U = 4;
+  for (uint32_t b = 0; b < len; b += 1024 * U) {
+    if (full()) break;
+    K r[U];
+    uint32_t act = 0;
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) {
+      const uint32_t i = b + u * 1024 + threadIdx.x;
+      r[u] = src[i < len ? i : 0u];
+      act |= i < len ? 1u << u : 0u;
+    }
+    count([&](const Part2& sel, uint32_t mask, int hshift) {
+      agg_count_each<K, U>(L, sel, mask, hshift, r, act, b + 1024 * U);
+    });
+  }
+}
+
+// Regroups src[0, len) into dst by the low `bits` bits of the hash: part q at
+// [at[q], at[q + 1]).  cur: as many words of LDS.
 template <class K>
-__global__ __launch_bounds__(1024) void k_count_slices(Plan a, const K* rem, uint32_t P, uint32_t S,
+__device__ void regroup(const K* src, uint32_t len, int bits, K* dst, uint32_t* at, uint32_t* cur) {
+  const uint32_t tid = threadIdx.x, parts = 1u << bits;
+  const uint64_t lt = (1ull << (tid & 63)) - 1ull;
+  constexpr uint32_t U = 4;
+  // use(remainder, part, lanes of the wave with the same part), by whole waves.
+  auto walk = [&](auto use) {
+    for (uint32_t b = 0; b < len; b += 1024 * U) {
+      K r[U];
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        const uint32_t i = b + u * 1024 + tid;
+        r[u] = src[i < len ? i : 0u];
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        const bool in = b + u * 1024 + tid < len;
+        const uint32_t q = rem_hash(r[u]) & (parts - 1u);
+        uint64_t m = __builtin_amdgcn_ballot_w64(in);
+        for (int k = 0; k < bits; ++k) {
+          const uint64_t one = __builtin_amdgcn_ballot_w64((q >> k) & 1u);
+          m &= (q >> k) & 1u ? one : ~one;
+        }
+        use(r[u], q, in ? m : 0ull);
+      }
+    }
+  };
+  if (tid < parts) cur[tid] = 0u;
+  __syncthreads();
+  walk([&](K, uint32_t q, uint64_t m) {
+    if (m && (m & lt) == 0) atomicAdd(&cur[q], (uint32_t)__builtin_popcountll(m));
+  });
+  __syncthreads();
+  if (tid == 0) {
+    uint32_t run = 0;
+    for (uint32_t q = 0; q < parts; ++q) {
+      const uint32_t c = cur[q];
+      at[q] = cur[q] = run;
+      run += c;
+    }
+    at[parts] = run;
+  }
+  __syncthreads();
+  walk([&](K r, uint32_t q, uint64_t m) {
+    uint32_t o = 0;
+    if (m && (m & lt) == 0) o = atomicAdd(&cur[q], (uint32_t)__builtin_popcountll(m));
+    o = (uint32_t)__shfl((int)o, m ? __builtin_ctzll(m) : 0);
+    if (m) dst[o + (uint32_t)__builtin_popcountll(m & lt)] = r;
+  });
+  __syncthreads();
+}
+
+// One slice of a partition.  A slice with more distinct remainders than the
+// table takes is regrouped by hash (through ukey's share of it, which holds
+// nothing yet) and counted part by part; the parts' n-grams gather where the
+// remainders were.  The table is given up as soon as probes get long, and how
+// far the walk had come says how many parts there have to be.  (Halving, with a
+// walk over the slice for each part and for each level above them, took 10.1 ms
+// a call for the 3-grams of 2^26 Zipf tokens, 33.6 and 58.5 for the 3- and 4-grams
+// of 200M; a walk for each of the right number of parts 3.4, 11.1 and 14; this
+// way 2.96, 7.3 and 7.5.)
+template <class K>
+__global__ __launch_bounds__(1024) void k_count_slices(Plan a, K* rem, uint32_t P, uint32_t S,
                                                        K* ukey, uint32_t* ucnt) {
   __shared__ Agg<K> L;
+  __shared__ uint32_t s_at[(1 << kMaxSplit) + 1], s_cur[1 << kMaxSplit];
   if (blockIdx.x >= a.first[P]) return;
   const uint32_t p = a.part[blockIdx.x];
   const uint32_t beg = a.start[p] + (blockIdx.x - a.first[p]) * S;
   const uint32_t len = min(S, a.start[p + 1] - beg);
-  const K* src = rem + beg;
-  auto feed = [&](auto count, auto full) {
-    constexpr uint32_t U = 4;
-    for (uint32_t b = 0; b < len; b += 1024 * U) {
-      if (full()) break;
-      K r[U];
-      uint32_t act = 0;
-#pragma unroll
-      for (uint32_t u = 0; u < U; ++u) {
-        const uint32_t i = b + u * 1024 + threadIdx.x;
-        r[u] = src[i < len ? i : 0u];
-        act |= i < len ? 1u << u : 0u;
-      }
-      count([&](const Part2& sel, uint32_t mask, int hshift) {
-        agg_count_each<K, U>(L, sel, mask, hshift, r, act);
-      });
+  rem += beg;
+  ukey += beg;
+  ucnt += beg;
+  if (threadIdx.x == 0) L.out = 0u;
+  const TableSize t = agg_table<K>(len);
+  const uint32_t over = agg_walk(L, Part2{0, 0u, 0ull}, t, [&](auto count, auto full) {
+    feed_rems(L, rem, len, count, full);
+  });
+  if (!over) {
+    agg_emit(L, t, ukey, ucnt);
+  } else {
+    const int bits = split_bits(len, over);
+    regroup(rem, len, bits, ukey, s_at, s_cur);
+    for (uint32_t q = 0; q < 1u << bits; ++q) {
+      const uint32_t b = s_at[q], n = s_at[q + 1] - b;
+      if (n == 0) continue;
+      agg_count(L, Part2{bits, q, 0ull}, n, [&](auto count, auto full) {
+        feed_rems(L, ukey + b, n, count, full);
+      }, rem, ucnt, a.state + kStFault);
     }
-  };
-  const uint32_t n = agg_count<K>(L, len, feed, ukey + beg, ucnt + beg, a.state + kStFault);
-  if (threadIdx.x == 0) a.nslice[blockIdx.x] = n;
+    for (uint32_t e = threadIdx.x; e < L.out; e += 1024) ukey[e] = rem[e];
+  }
+  if (threadIdx.x == 0) a.nslice[blockIdx.x] = L.out;
 }
 
 // The partial counts of a partition counted in several slices, added up
@@ -727,13 +870,19 @@ template <class K>
 __global__ __launch_bounds__(1024) void k_count_merge(Plan a, const K* ukey, const uint32_t* ucnt,
                                                       uint32_t S, K* mkey, uint32_t* mcnt) {
   __shared__ Agg<K> L;
+  __shared__ uint32_t s_len;
   const uint32_t p = blockIdx.x, f = a.first[p], ns = a.first[p + 1] - f, beg = a.start[p];
   if (ns <= 1) {
     if (threadIdx.x == 0) a.nuniq[p] = ns ? a.nslice[f] : 0u;
     return;
   }
-  const uint32_t len = a.start[p + 1] - beg;
+  if (threadIdx.x == 0) s_len = 0u;
+  __syncthreads();
+  for (uint32_t j = threadIdx.x; j < ns; j += 1024) atomicAdd(&s_len, a.nslice[f + j]);
+  __syncthreads();
+  const uint32_t len = s_len;
   auto feed = [&](auto count, auto full) {
+    uint32_t fed = 0;
     for (uint32_t j = 0; j < ns; ++j) {
       const uint32_t n = a.nslice[f + j], s = beg + j * S;
       for (uint32_t b = 0; b < n; b += 1024) {
@@ -743,13 +892,15 @@ __global__ __launch_bounds__(1024) void k_count_merge(Plan a, const K* ukey, con
         const K r = ukey[q];
         const uint32_t w = ucnt[q];
         count([&](const Part2& sel, uint32_t mask, int hshift) {
-          agg_add<K>(L, sel, mask, hshift, r, w, i < n);
+          agg_add<K>(L, sel, mask, hshift, r, w, i < n, fed + b + 1024);
         });
       }
+      fed += n;
     }
   };
-  const uint32_t n = agg_count<K>(L, len, feed, mkey + beg, mcnt + beg, a.state + kStFault);
-  if (threadIdx.x == 0) a.nuniq[p] = n;
+  if (threadIdx.x == 0) L.out = 0u;
+  agg_count(L, Part2{0, 0u, 0ull}, len, feed, mkey + beg, mcnt + beg, a.state + kStFault);
+  if (threadIdx.x == 0) a.nuniq[p] = L.out;
 }
 
 // The distinct n-grams: partition p's nuniq[p] keys and counts, in one of two
@@ -1438,10 +1589,11 @@ struct Scratch {
     hipError_t e_ = (call);                                                          \
     if (e_ != hipSuccess) return fail(TFE_ERR_HIP, "%s: %s", what, hipGetErrorString(e_)); \
   } while (0)
-// Partitions for nwin windows: enough that a partition's distinct n-grams
-// fit the LDS table (about 6000 of 8192 64-bit entries even when every
-// window is distinct; for n <= 2, where most windows repeat, 32768 windows
-// against 16384 entries), within what the scatter's LDS counters allow.
+// Partitions for nwin windows: as many as let a partition's distinct n-grams
+// fit the LDS table (6000 windows against 8192 64-bit entries; for n <= 2,
+// where most windows repeat, 32768 against 16384), within what the scatter's
+// LDS counters allow.  Beyond (from 24.6M windows for n > 2), and where few
+// 2-grams repeat, a partition's block splits it further.
 int part_bits(uint64_t nwin, int n) {
   const uint64_t mean = n <= 2 ? 32768 : 6000;
   int b = kMinPartBits;
