@@ -20,7 +20,7 @@
 //   4. the n-grams with count >= c* become records that compare in rank
 //      order: count descending, then tuple (when far more n-grams have
 //      count c* than are needed, a radix select over their tuples first
-//      finds the last one needed);
+//      cuts off most of the others);
 //   5. the records are ranked by one bucket sort (splitters from a sample,
 //      LDS sorts), which writes ranks [skip, skip + top) as tuples and
 //      counts; rankings of millions of records take a radix sort instead.
@@ -401,6 +401,7 @@ enum {
   kStCstar, kStR, kStNeed, kStAbove, kStEqual, kStU,  // k_sel_small
   kStPlaced,                                          // records gathered so far
   kStTieHi, kStTieLo, kStTieNeed,                     // tie selection: key prefix, rank in it
+  kStTieDone,                                         // 0, or how many records it leaves
   kStFault,
   kStWords = 16
 };
@@ -1049,10 +1050,12 @@ __device__ __forceinline__ void write_rank(const Rec2& r, int n, int32_t* t, int
 }
 
 // Tie selection, digit d (9 bits, from the oldest token's high bits) of the
-// tuples with count c* whose earlier digits are the ones decided.
+// tuples with count c* whose earlier digits are the ones decided.  Nothing
+// once the selection is done.
 template <int NG>
 __global__ __launch_bounds__(1024) void k_tie_hist(Uniq<Rem<NG>> u, int pbits, int d) {
   __shared__ uint32_t h[512];
+  if (u.a.state[kStTieDone]) return;
   if (threadIdx.x < 512) h[threadIdx.x] = 0u;
   __syncthreads();
   const uint32_t cstar = (uint32_t)u.a.state[kStCstar];
@@ -1077,8 +1080,13 @@ __global__ __launch_bounds__(1024) void k_tie_hist(Uniq<Rem<NG>> u, int pbits, i
 }
 
 // One block: the digit that holds the needed tuple; clears the histogram.
-__global__ __launch_bounds__(512) void k_tie_pick(Plan a, int d) {
+// Once at most `slack` tuples share the digits decided, all of them are taken
+// (the ranking sorts out which are needed): every pass reads all the counts
+// and keys at c*, and the six for the 3-grams of 2^26 tokens drawn evenly took
+// 1.13 ms of 4.45, where one is enough.
+__global__ __launch_bounds__(512) void k_tie_pick(Plan a, int d, uint32_t slack) {
   __shared__ uint32_t s_wave[8];
+  if (a.state[kStTieDone]) return;
   const uint32_t t = threadIdx.x;
   const uint64_t need = a.state[kStTieNeed];
   const uint32_t v = a.tie[t];
@@ -1086,13 +1094,18 @@ __global__ __launch_bounds__(512) void k_tie_pick(Plan a, int d) {
   const uint64_t ex = block_scan_excl<512>(v, s_wave, &tot);
   a.tie[t] = 0u;
   if (ex < need && need <= ex + v) {
-    a.state[d < 4 ? kStTieHi : kStTieLo] |= (uint64_t)t << (27 - 9 * (d & 3));
+    const int sh = 27 - 9 * (d & 3);
+    const bool done = v <= slack;
+    const uint64_t rest = done ? (1ull << sh) - 1ull : 0ull;
+    a.state[d < 4 ? kStTieHi : kStTieLo] |= (uint64_t)t << sh | rest;
+    if (done && d < 4) a.state[kStTieLo] = (1ull << 36) - 1ull;
     a.state[kStTieNeed] = need - ex;
+    if (done) a.state[kStTieDone] = a.state[kStAbove] + (a.state[kStNeed] - (need - ex)) + v;
   }
 }
 
 // Records of the n-grams with count above c*, and of those at c* (every one;
-// with `tie`, up to the selected tuple), in no particular order.  A block
+// with `tie`, up to the selected prefix), in no particular order.  A block
 // counts its share first and takes its places with one atomic.
 template <int NG>
 __global__ __launch_bounds__(1024) void k_gather(Uniq<Rem<NG>> u, int pbits, uint32_t tie,
@@ -1663,14 +1676,21 @@ tfe_status ngram_top_n(const int32_t* tokens, uint64_t nwin, int32_t vocab, uint
   // digit by digit; few: they are ranked with the rest.
   const bool tie = st[kStCstar] < (uint64_t)kSelBins - 1 &&
                    st[kStEqual] > 4 * st[kStNeed] + (1u << 20);
+  uint64_t nrec = st[kStAbove] + st[kStEqual];
   if (tie) {
-    for (int d = 0; d < 2 * NG; ++d) {
+    // Tuples that share all tokens but the newest are 2^18 at most: the digits
+    // before it always reach the slack.
+    const uint32_t slack = (1u << 18) + (uint32_t)(ranks / 4);
+    for (int d = 0; d < 2 * (NG - 1); ++d) {
       hipLaunchKernelGGL(k_tie_hist<NG>, dim3(walkers), dim3(1024), 0, s, u, ts.pbits, d);
-      hipLaunchKernelGGL(k_tie_pick, dim3(1), dim3(512), 0, s, a, d);
+      hipLaunchKernelGGL(k_tie_pick, dim3(1), dim3(512), 0, s, a, d, slack);
     }
     BUILD_HIP(hipGetLastError(), "tie launches");
+    BUILD_HIP(hipMemcpyAsync(&nrec, a.state + kStTieDone, sizeof nrec, hipMemcpyDeviceToHost, s),
+              "copy");
+    BUILD_HIP(hipStreamSynchronize(s), "sync");
+    if (nrec < ranks) return fail(TFE_ERR_HIP, "tie selection");
   }
-  const uint64_t nrec = tie ? ranks : st[kStAbove] + st[kStEqual];
   R* rec = sc.get<R>(nrec);
   R* rec2 = sc.get<R>(nrec);
   if (!rec || !rec2) return fail(TFE_ERR_OOM, "rank arrays");

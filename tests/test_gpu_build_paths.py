@@ -38,6 +38,25 @@ def test_uniform_streams(n, N, vocab, skip, top):
     check(uniform(N + n, N, vocab), vocab, n, skip, top)
 
 
+@pytest.mark.parametrize("n,prefix,first", [
+    (2, [], 1 << 18), (2, [], 512), (3, [7], 1 << 18), (3, [], 512), (3, [7], 512),
+    (4, [7], 1 << 18), (4, [7, 9], 1 << 18), (4, [7, 9], 512)])
+def test_ties_that_share_their_oldest_tokens(n, prefix, first):
+    """1.5M windows, nearly all seen once, whose oldest tokens (and with first = 512
+    the high digit of the next) are the same: the tie selection goes through
+    one digit to all before the newest token's."""
+    rng = np.random.default_rng(first + 10 * n + len(prefix))
+    w = rng.integers(0, 1 << 18, (1500000, n + 1)).astype(np.int32)
+    w[:, :len(prefix)] = prefix
+    w[:, len(prefix)] = rng.integers(0, first, len(w))
+    w[:, n] = -1
+    key = w[:, n - 2].astype(np.int64) << 18 | w[:, n - 1]  # the tokens that differ, and more
+    assert (np.unique(key, return_counts=True)[1] == 1).sum() > (1 << 20) + 4 * 3000
+    extra = w[rng.permutation(len(w))[:1000]]  # and some above the ties
+    tok = np.concatenate([w, extra, extra]).ravel()
+    check(tok, 1 << 18, n, 5, 3000)
+
+
 @pytest.mark.parametrize("n", [1, 2, 3, 4])
 def test_one_ngram_fills_a_partition(n):
     """Half the stream repeats one token: its partition spans several slices,
