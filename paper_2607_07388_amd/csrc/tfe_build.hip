@@ -671,19 +671,22 @@ __device__ __forceinline__ TableSize agg_table(uint32_t len) {
   return t;
 }
 
-// Counts, in a cleared table, the remainders that sel takes among those that
-// feed(count, full) has count(f) add (f is called by whole waves with the
-// table's parameters; full() is true once the table has overflowed).  Returns
-// 0, or how much had been fed when the table was given up (block-uniform).
+// Counts, in a cleared table (or on in one, with `on`), the remainders that sel
+// takes among those that feed(count, full) has count(f) add (f is called by
+// whole waves with the table's parameters; full() is true once the table has
+// overflowed).  Returns 0, or how much had been fed when the table was given up
+// (block-uniform).
 template <class K, class Feed>
 __device__ __forceinline__ uint32_t agg_walk(Agg<K>& L, const Part2& sel, const TableSize& t,
-                                             Feed feed) {
-  for (uint32_t e = threadIdx.x; e < t.slots; e += 1024) {
-    L.key[e] = (K)~(K)0;
-    L.cnt[e] = 0u;
+                                             Feed feed, bool on = false) {
+  if (!on) {
+    for (uint32_t e = threadIdx.x; e < t.slots; e += 1024) {
+      L.key[e] = (K)~(K)0;
+      L.cnt[e] = 0u;
+    }
+    if (threadIdx.x == 0) L.over = 0u;
+    __syncthreads();
   }
-  if (threadIdx.x == 0) L.over = 0u;
-  __syncthreads();
   feed([&](auto f) { f(sel, t.slots - 1, t.hshift); },
        [&] { return read_word(&L.over) != 0u; });
   __syncthreads();
@@ -830,7 +833,7 @@ __device__ void regroup(const K* src, uint32_t len, int bits, K* dst, uint32_t* 
 // walk over the slice for each part and for each level above them, took 10.1 ms
 // a call for the 3-grams of 2^26 Zipf tokens, 33.6 and 58.5 for the 3- and 4-grams
 // of 200M; a walk for each of the right number of parts 3.4, 11.1 and 14; this
-// way 2.96, 7.3 and 7.5.)
+// way 3.0, 7.2 and 7.1.)
 template <class K>
 __global__ __launch_bounds__(1024) void k_count_slices(Plan a, K* rem, uint32_t P, uint32_t S,
                                                        K* ukey, uint32_t* ucnt) {
@@ -845,9 +848,30 @@ __global__ __launch_bounds__(1024) void k_count_slices(Plan a, K* rem, uint32_t 
   ucnt += beg;
   if (threadIdx.x == 0) L.out = 0u;
   const TableSize t = agg_table<K>(len);
-  const uint32_t over = agg_walk(L, Part2{0, 0u, 0ull}, t, [&](auto count, auto full) {
-    feed_rems(L, rem, len, count, full);
-  });
+  const Part2 all{0, 0u, 0ull};
+  // Most 3- and 4-grams of long streams are distinct: where the first windows
+  // are (7/8 of them), and say that the slice's fill the table, the rest of the
+  // filling is left out.
+  const uint32_t first = sizeof(K) == 8 && len > t.slots / 8 * 7 ? 4096u : 0u;
+  uint32_t over = 0;
+  if (first) {
+    if (threadIdx.x == 0) s_cur[0] = 0u;
+    agg_walk(L, all, t, [&](auto count, auto full) { feed_rems(L, rem, first, count, full); });
+    uint32_t n = 0;
+    for (uint32_t e = threadIdx.x; e < t.slots; e += 1024)
+      n += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(L.cnt[e] != 0u));
+    if ((threadIdx.x & 63) == 0) atomicAdd(&s_cur[0], n);
+    __syncthreads();
+    const uint32_t fills = (uint32_t)((uint64_t)(t.slots / 8 * 7) * first / s_cur[0]);
+    if (s_cur[0] >= first / 8 * 7 && fills <= len) over = fills;
+    __syncthreads();  // s_cur is read before the regrouping clears it
+  }
+  if (!over) {
+    over = agg_walk(L, all, t, [&](auto count, auto full) {
+      feed_rems(L, rem + first, len - first, count, full);
+    }, first != 0);
+    if (over) over += first;
+  }
   if (!over) {
     agg_emit(L, t, ukey, ucnt);
   } else {

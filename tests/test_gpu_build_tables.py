@@ -83,16 +83,20 @@ def stream(windows, copies, rng):
     return np.concatenate([w, np.full((len(w), 1), -1, np.int32)], axis=1).ravel()
 
 
-@pytest.mark.parametrize("n,count,twice", [
-    (2, 60000, 0), (3, 60000, 20000), (4, 60000, 20000),  # several slices, all too full; so are merges
-    (3, 9000, 500), (4, 16000, 0),                        # one slice, one table too few
-    (2, 16384, 0), (3, 8192, 0), (4, 8192, 0),            # a window for every entry
+@pytest.mark.parametrize("n,count,twice,heavy", [
+    (2, 60000, 0, 1), (3, 60000, 20000, 1), (4, 60000, 20000, 1),  # several slices, all too full; merges too
+    (3, 9000, 500, 1), (4, 16000, 0, 1),                # one slice, one table too few
+    (2, 16384, 0, 1), (3, 8192, 0, 1), (4, 8192, 0, 1), # a window for every entry
+    (3, 7200, 0, 1), (4, 7100, 0, 1),                   # just more and less than 7/8 of the entries
+    (3, 9500, 0, 3000), (4, 12000, 0, 4000),            # too many, though the first windows repeat
+    (3, 4200, 0, 9000), (4, 5000, 0, 11000),            # not too many
 ])
-def test_distinct_ngrams_of_one_partition(n, count, twice):
+def test_distinct_ngrams_of_one_partition(n, count, twice, heavy):
     rng = np.random.default_rng(1000 * n + count)
     rem = rng.choice(1 << min(LOW + 18 * (n - 1), 40), count + 200, replace=False)[:count]
     copies = np.ones(count, np.int64)
     copies[rng.permutation(count)[:twice]] = 2
+    copies[0] = heavy
     tok = stream(windows_of(5, rem, n), copies, rng)
     assert tok.size < 512 * 16384 // 2  # 512 partitions, slices of 16384
     check(tok, 1 << 18, n, 3, 2 * count)
