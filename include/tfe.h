@@ -355,7 +355,9 @@ tfe_status tfe_head_topk_noalloc(const void *w_pref, int32_t vocab, int32_t dim,
  *               stream has fewer than skip + top distinct tuples)
  * Synchronous: returns once the outputs are complete.  Its scratch (device
  * memory of the current device: about 17 bytes per token, 26 for 3- and
- * 4-grams, and 18 or 34 per n-gram ranked)
+ * 4-grams, and 16 or 32 per n-gram ranked, 16 at most when those are more than
+ * 2^20; n-grams that share the last rank's count are ranked along, at most 2^20
+ * of them and three times the ranks wanted)
  * stays with the library after the call and is reused by later calls of a
  * similar size, until tfe_ngram_release; a call that finds no fitting idle
  * buffer first returns the idle ones.  Safe to call from several host

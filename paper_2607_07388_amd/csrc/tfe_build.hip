@@ -23,7 +23,8 @@
 //      cuts off most of the others);
 //   5. the records are ranked by one bucket sort (splitters from a sample,
 //      LDS sorts), which writes ranks [skip, skip + top) as tuples and
-//      counts; rankings of millions of records take a radix sort instead.
+//      counts; of more than a million records only the few with counts above
+//      511, the others, packed tighter, by a radix sort.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -383,7 +384,7 @@ __global__ __launch_bounds__(kPartThreads) void k_part_scatter(TokSrc ts, uint64
 
 // Where everything lies, in one small device buffer (plan_words words).
 constexpr int kSelBins = 4096;
-constexpr uint32_t kMaxBuckets = 4096;
+constexpr uint32_t kMaxBuckets = 1024;
 struct Plan {
   uint32_t* start;   // [P + 1]: partition p holds remainders [start[p], start[p + 1])
   uint32_t* first;   // [P + 1]: its slices are [first[p], first[p + 1])
@@ -399,7 +400,8 @@ struct Plan {
 };
 enum {
   kStCstar, kStR, kStNeed, kStAbove, kStEqual, kStU,  // k_sel_small
-  kStPlaced,                                          // records gathered so far
+  kStPlaced, kStPlacedLow,                            // records gathered so far
+  kStHigh,                                            // n-grams with count above kLowMax
   kStTieHi, kStTieLo, kStTieNeed,                     // tie selection: key prefix, rank in it
   kStTieDone,                                         // 0, or how many records it leaves
   kStFault,
@@ -863,7 +865,7 @@ __global__ __launch_bounds__(1024) void k_count_slices(Plan a, K* rem, uint32_t 
     if ((threadIdx.x & 63) == 0) atomicAdd(&s_cur[0], n);
     __syncthreads();
     const uint32_t fills = (uint32_t)((uint64_t)(t.slots / 8 * 7) * first / s_cur[0]);
-    if (s_cur[0] >= first / 8 * 7 && fills <= len) over = fills;
+    if (s_cur[0] >= first / 4 * 3 && fills <= len / 8 * 7) over = fills;
     __syncthreads();  // s_cur is read before the regrouping clears it
   }
   if (!over) {
@@ -1000,6 +1002,7 @@ __global__ __launch_bounds__(1024) void k_sel_hist(Uniq<K> u) {
 // largest count, the number above it, how many n-grams of count c* belong to
 // the R ranks and how many there are.  c* = kSelBins - 1 stands for every
 // count from there on.
+constexpr uint32_t kLowMax = 511;  // largest count of a packed record (below)
 __global__ __launch_bounds__(1024) void k_sel_small(Plan a, uint64_t want) {
   __shared__ uint32_t s_wave[16];
   const uint32_t t = threadIdx.x;
@@ -1015,6 +1018,8 @@ __global__ __launch_bounds__(1024) void k_sel_small(Plan a, uint64_t want) {
     a.state[kStU] = U;
     a.state[kStR] = R;
   }
+  static_assert((kSelBins - 1 - kLowMax) % 4 == 0, "the first bin of a thread");
+  if (t == (kSelBins - 1 - kLowMax) / 4) a.state[kStHigh] = ex;
   for (int k = 0; k < 4; ++k) {
     if (ex < R && R <= ex + v[k]) {
       a.state[kStCstar] = kSelBins - 1 - (4 * t + k);
@@ -1128,18 +1133,16 @@ __global__ __launch_bounds__(512) void k_tie_pick(Plan a, int d, uint32_t slack)
   }
 }
 
-// Records of the n-grams with count above c*, and of those at c* (every one;
-// with `tie`, up to the selected prefix), in no particular order.  A block
-// counts its share first and takes its places with one atomic.
-template <int NG>
-__global__ __launch_bounds__(1024) void k_gather(Uniq<Rem<NG>> u, int pbits, uint32_t tie,
-                                                 Rec<NG>* out, uint32_t cap) {
-  __shared__ uint32_t s_n;
+// Goes twice through the distinct n-grams, once to count and once to place
+// them: use(second, partition, remainders, index, count, kept), by whole waves.
+// Kept are those with count above c* and those at c* (every one; with `tie`, up
+// to the selected prefix).  between() stands between the two.
+template <int NG, class Use, class Between>
+__device__ __forceinline__ void gather_walk(const Uniq<Rem<NG>>& u, int pbits, uint32_t tie, Use use,
+                                            Between between) {
   const uint32_t cstar = (uint32_t)u.a.state[kStCstar];
   const uint64_t th = u.a.state[kStTieHi], tl = u.a.state[kStTieLo];
-  const int lane = threadIdx.x & 63;
-  const uint64_t lt = (1ull << lane) - 1ull;
-  auto walk = [&](auto use) {
+  auto walk = [&](auto second) {
     for (uint32_t p = blockIdx.x; p < u.P; p += gridDim.x) {
       const Rem<NG>* k;
       const uint32_t* c;
@@ -1157,64 +1160,127 @@ __global__ __launch_bounds__(1024) void k_gather(Uniq<Rem<NG>> u, int pbits, uin
             const uint64_t hi = key_hi(x);
             keep = hi < th || (hi == th && key_lo(x) <= tl);
           }
-          use(p, k, i, ci, keep);
+          use(second, p, k, i, ci, keep);
         }
       }
     }
   };
+  walk(std::false_type{});
+  between();
+  walk(std::true_type{});
+}
+
+// The places of a wave's kept lanes behind *n (LDS).
+__device__ __forceinline__ uint32_t append(uint32_t* n, bool keep) {
+  const int lane = threadIdx.x & 63;
+  const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
+  uint32_t o = 0;
+  if (m && lane == 0) o = atomicAdd(n, (uint32_t)__builtin_popcountll(m));
+  return __builtin_amdgcn_readfirstlane(o) + (uint32_t)__builtin_popcountll(m & ((1ull << lane) - 1ull));
+}
+// A block's share *n becomes its first place among all of them.
+__device__ __forceinline__ void take_places(uint32_t* n, uint64_t* placed) {
+  *n = (uint32_t)atomicAdd((unsigned long long*)placed, (unsigned long long)*n);
+}
+
+// Records of the kept n-grams, in no particular order.  A block counts its
+// share first and takes its places with one atomic.
+template <int NG>
+__global__ __launch_bounds__(1024) void k_gather(Uniq<Rem<NG>> u, int pbits, uint32_t tie,
+                                                 Rec<NG>* out, uint32_t cap) {
+  __shared__ uint32_t s_n;
   if (threadIdx.x == 0) s_n = 0u;
   __syncthreads();
-  walk([&](uint32_t, const Rem<NG>*, uint32_t, uint32_t, bool keep) {
-    const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
-    if (m && lane == 0) atomicAdd(&s_n, (uint32_t)__builtin_popcountll(m));
-  });
+  gather_walk<NG>(
+      u, pbits, tie,
+      [&](auto second, uint32_t p, const Rem<NG>* k, uint32_t i, uint32_t ci, bool keep) {
+        const uint32_t o = append(&s_n, keep);
+        if (decltype(second)::value && keep && o < cap) {
+          uint32_t x[4];
+          join_window<NG>(p, k[i], pbits, x);
+          make_rec(&out[o], ci, x);
+        }
+      },
+      [&] {
+        __syncthreads();
+        if (threadIdx.x == 0) take_places(&s_n, u.a.state + kStPlaced);
+        __syncthreads();
+      });
+}
+
+// The same for long rankings: records of the n-grams with count above kLowMax,
+// and the others packed: kLowMax - count (9 bits) and up to three tokens in a
+// word, the fourth in one of its own.
+template <int NG>
+constexpr int packed_tokens() { return 18 * (NG < 3 ? NG : 3); }
+template <int NG>
+__global__ __launch_bounds__(1024) void k_gather_long(Uniq<Rem<NG>> u, int pbits, uint32_t tie,
+                                                      Rec<NG>* high, uint32_t nhigh, uint64_t* low,
+                                                      uint32_t* low3, uint32_t nlow) {
+  __shared__ uint32_t s_n[2];
+  if (threadIdx.x < 2) s_n[threadIdx.x] = 0u;
   __syncthreads();
-  if (threadIdx.x == 0)
-    s_n = (uint32_t)atomicAdd((unsigned long long*)(u.a.state + kStPlaced), (unsigned long long)s_n);
-  __syncthreads();
-  walk([&](uint32_t p, const Rem<NG>* k, uint32_t i, uint32_t ci, bool keep) {
-    const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
-    uint32_t o = 0;
-    if (m && lane == 0) o = atomicAdd(&s_n, (uint32_t)__builtin_popcountll(m));
-    o = __builtin_amdgcn_readfirstlane(o) + (uint32_t)__builtin_popcountll(m & lt);
-    if (keep && o < cap) {
-      uint32_t x[4];
-      join_window<NG>(p, k[i], pbits, x);
-      Rec<NG> r;
-      make_rec(&r, ci, x);
-      out[o] = r;
-    }
-  });
+  gather_walk<NG>(
+      u, pbits, tie,
+      [&](auto second, uint32_t p, const Rem<NG>* k, uint32_t i, uint32_t ci, bool keep) {
+        const bool hi = keep && ci > kLowMax, lo = keep && ci <= kLowMax;
+        const uint32_t oh = append(&s_n[0], hi), ol = append(&s_n[1], lo);
+        if (!decltype(second)::value) return;
+        uint32_t x[4];
+        if (hi && oh < nhigh) {
+          join_window<NG>(p, k[i], pbits, x);
+          make_rec(&high[oh], ci, x);
+        } else if (lo && ol < nlow) {
+          join_window<NG>(p, k[i], pbits, x);
+          uint64_t w = kLowMax - ci;
+#pragma unroll
+          for (int q = 0; q < (NG < 3 ? NG : 3); ++q) w = (w << 18) | x[q];
+          low[ol] = w;
+          if (NG == 4) low3[ol] = x[3];
+        }
+      },
+      [&] {
+        __syncthreads();
+        if (threadIdx.x < 2) take_places(&s_n[threadIdx.x], u.a.state + kStPlaced + threadIdx.x);
+        __syncthreads();
+      });
 }
 
 // ---- 5. ranking ------------------------------------------------------------------
 
 // Bucket sort: splitters from a sorted sample (4 records per bucket), each
 // record's bucket by binary search, then one LDS sort per bucket, which
-// writes the ranks asked for.  A bucket holds about kBucketMean records of at
-// most kBucketCap (eight times that): larger ones, which a sample of
-// distinct records practically never leaves, are ranked by counting.
+// writes the ranks asked for.  A bucket holds about kBucketMean records, at
+// most kBucketCap in LDS; a larger one (eight times the mean, between five
+// samples taken at even distances from records in no order: one in 10^10) is
+// sorted in memory.
 constexpr uint32_t kBucketMean = 1024;
 constexpr uint32_t kBucketCap = 8192;
-template <class R>
-constexpr uint32_t max_buckets() { return sizeof(R) == 8 ? 4096u : 2048u; }
-// Most records the bucket sort takes (2048 per bucket on average).
-template <class R>
-constexpr uint64_t bucket_sort_max() { return 2048ull * max_buckets<R>(); }
+// Most records the bucket sort takes.  Beyond, the radix sort of packed records
+// is faster.  All the n-grams of N evenly drawn tokens, bucket sort / radix sort,
+// us a call: 2-grams 263 / 263 at N = 800000, 359 / 289 at 1.4M; 3-grams
+// 333 / 314, 492 / 351; 4-grams 335 / 386, 493 / 419.
+constexpr uint64_t kBucketSortMax = (uint64_t)kBucketMean * kMaxBuckets;
 
-// Bitonic sort of a[0, N2) in LDS, ascending; N2 a power of two.  (Block
-// barriers only where a step leaves a wave's 128 elements changed nothing in
-// the bucket sorts and took 4 of 41 us off the sample's.)
+// Bitonic sort of a[0, m), ascending, in LDS or in memory.  Every comparison
+// puts the smaller record first (the first step of a merge compares mirrored
+// places), so the places from m to the next power of two, which would hold
+// larger records than all others, need not exist.  (Block barriers only where a
+// step leaves a wave's 128 elements changed nothing in the bucket sorts and
+// took 4 of 41 us off the sample's.)
 template <class R>
-__device__ void lds_sort(R* a, uint32_t N2) {
+__device__ __forceinline__ void bitonic_sort(R* a, uint32_t m) {
+  uint32_t N2 = 2;
+  while (N2 < m) N2 <<= 1;
   for (uint32_t size = 2; size <= N2; size <<= 1) {
     for (uint32_t stride = size >> 1; stride > 0; stride >>= 1) {
       __syncthreads();
       for (uint32_t e = threadIdx.x; e < N2 / 2; e += 1024) {
         const uint32_t i = 2 * e - (e & (stride - 1));
-        const uint32_t j = i + stride;
+        const uint32_t j = stride == size >> 1 ? i ^ (size - 1) : i + stride;
+        if (j >= m) continue;
         const R x = a[i], y = a[j];
-        if (before(y, x) == ((i & size) == 0)) {
+        if (before(y, x)) {
           a[i] = y;
           a[j] = x;
         }
@@ -1228,10 +1294,10 @@ __device__ void lds_sort(R* a, uint32_t N2) {
 template <class R>
 __global__ __launch_bounds__(1024) void k_bk_sample(const R* rec, uint64_t K, uint32_t nb,
                                                     R* split) {
-  __shared__ R s[4 * max_buckets<R>()];
+  __shared__ R s[4 * kMaxBuckets];
   const uint32_t ns = 4 * nb;
   for (uint32_t e = threadIdx.x; e < ns; e += 1024) s[e] = rec[(uint64_t)e * K / ns];
-  lds_sort(s, ns);
+  bitonic_sort(s, ns);
   for (uint32_t b = 1 + threadIdx.x; b < nb; b += 1024) split[b - 1] = s[4 * b];
 }
 
@@ -1241,8 +1307,8 @@ constexpr uint32_t kBkTile = 4096;
 template <class R>
 __global__ __launch_bounds__(1024) void k_bk_hist(Plan a, const R* rec, uint64_t K, uint32_t nb,
                                                   const R* split, uint16_t* bkt) {
-  __shared__ R s[max_buckets<R>()];
-  __shared__ uint32_t c[max_buckets<R>()];
+  __shared__ R s[kMaxBuckets];
+  __shared__ uint32_t c[kMaxBuckets];
   for (uint32_t e = threadIdx.x; e < nb; e += 1024) {
     s[e] = e + 1 < nb ? split[e] : last_rec<R>();
     c[e] = 0u;
@@ -1268,9 +1334,9 @@ __global__ __launch_bounds__(1024) void k_bk_hist(Plan a, const R* rec, uint64_t
 template <class R>
 __global__ __launch_bounds__(1024) void k_bk_scatter(Plan a, const R* rec, uint64_t K, uint32_t nb,
                                                      const uint16_t* bkt, R* out) {
-  __shared__ uint32_t c[max_buckets<R>()], base[max_buckets<R>()];
+  __shared__ uint32_t c[kMaxBuckets], base[kMaxBuckets];
   __shared__ uint32_t s_wave[16];
-  constexpr uint32_t PER = max_buckets<R>() / 1024;
+  constexpr uint32_t PER = kMaxBuckets / 1024;
   const uint32_t tid = threadIdx.x;
   uint32_t n[PER], sum = 0;
 #pragma unroll
@@ -1309,33 +1375,30 @@ __global__ __launch_bounds__(1024) void k_bk_scatter(Plan a, const R* rec, uint6
   }
 }
 
-// Sorts one bucket (whole = 0: the only one) and writes its ranks in
-// [skip, R).
+// Sorts one bucket (whole > 0: all of the records, the only one) and writes its
+// ranks in [skip, ranks).
 template <class R>
-__global__ __launch_bounds__(1024) void k_bk_sort(Plan a, const R* rec, uint32_t whole,
-                                                  uint64_t skip, uint64_t ranks, int n,
-                                                  int32_t* tuples, int64_t* counts) {
+__global__ __launch_bounds__(1024) void k_bk_sort(Plan a, R* rec, uint32_t whole, uint64_t skip,
+                                                  uint64_t ranks, int n, int32_t* tuples,
+                                                  int64_t* counts) {
   __shared__ R s[kBucketCap];
   const uint32_t beg = whole ? 0u : a.bstart[blockIdx.x];
   const uint32_t m = whole ? whole : a.bstart[blockIdx.x + 1] - beg;
   if (m == 0 || beg >= ranks || (uint64_t)beg + m <= skip) return;
-  auto emit = [&](uint64_t rank, const R& r) {
-    if (rank >= skip && rank < ranks) write_rank(r, n, tuples + (rank - skip) * n, counts + (rank - skip));
-  };
-  if (m > kBucketCap) {
-    for (uint32_t e = threadIdx.x; e < m; e += 1024) {
-      const R x = rec[beg + e];
-      uint32_t r = 0;
-      for (uint32_t q = 0; q < m; ++q) r += before(rec[beg + q], x) ? 1u : 0u;
-      emit((uint64_t)beg + r, x);
-    }
-    return;
+  rec += beg;
+  const bool lds = m <= kBucketCap;
+  if (lds) {
+    for (uint32_t e = threadIdx.x; e < m; e += 1024) s[e] = rec[e];
+    bitonic_sort(s, m);
+  } else {
+    bitonic_sort(rec, m);
   }
-  uint32_t N2 = 2;
-  while (N2 < m) N2 <<= 1;
-  for (uint32_t e = threadIdx.x; e < N2; e += 1024) s[e] = e < m ? rec[beg + e] : last_rec<R>();
-  lds_sort(s, N2);
-  for (uint32_t e = threadIdx.x; e < m; e += 1024) emit((uint64_t)beg + e, s[e]);
+  for (uint32_t e = threadIdx.x; e < m; e += 1024) {
+    const R r = lds ? s[e] : rec[e];
+    const uint64_t rank = (uint64_t)beg + e;
+    if (rank >= skip && rank < ranks)
+      write_rank(r, n, tuples + (rank - skip) * n, counts + (rank - skip));
+  }
 }
 
 // Tiles of the radix sort: 512 threads (one per digit), 8 keys per thread
@@ -1354,7 +1417,8 @@ static_assert(kBins <= (uint32_t)kTileThreads, "one scatter thread per digit");
 
 // ---- 6. long rankings: stable LSD radix sort (9-bit digits) -----------------
 //
-// Records beyond what the bucket sort holds (millions of ranks asked for).
+// Packed records, where more than the bucket sort takes are ranked (millions of
+// ranks asked for).
 
 template <class K>
 __device__ __forceinline__ uint32_t digit_of(K k, int shift) {
@@ -1495,25 +1559,24 @@ __global__ __launch_bounds__(kTileThreads) void k_rs_scatter(const K* keys, cons
     if (PAIRS) vals_out[dst] = s_vals[PAIRS ? p : 0];
   }
 }
-// Words of records that the two radix key arrays hold, and back.
-__global__ __launch_bounds__(256) void k_split_rec2(const Rec2* rec, uint64_t K, uint64_t* hi,
-                                                    uint64_t* lo) {
-  const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < K) {
-    hi[i] = rec[i].hi;
-    lo[i] = rec[i].lo;
-  }
-}
 
-__global__ __launch_bounds__(256) void k_unpack(const uint64_t* hi, const uint64_t* lo,
-                                                uint64_t skip, uint64_t m, int n, int32_t* tuples,
-                                                int64_t* counts) {
-  const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= m) return;
-  if (lo)
-    write_rank(Rec2{hi[skip + i], lo[skip + i]}, n, tuples + i * n, counts + i);
-  else
-    write_rank(Rec1{hi[skip + i]}, n, tuples + i * n, counts + i);
+// Sorted packed records as ranks: record i is rank at + i - skip of the outputs.
+template <int NG>
+__global__ __launch_bounds__(256) void k_unpack(const uint64_t* low, const uint32_t* low3,
+                                                uint64_t from, uint64_t to, uint64_t at,
+                                                uint64_t skip, int32_t* tuples, int64_t* counts) {
+  const uint64_t i = from + (uint64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= to) return;
+  uint64_t w = low[i];
+  const uint64_t rank = at + i - skip;
+  int32_t* t = tuples + rank * NG;
+#pragma unroll
+  for (int q = (NG < 3 ? NG : 3) - 1; q >= 0; --q) {
+    t[q] = (int32_t)(w & kTok);
+    w >>= 18;
+  }
+  if (NG == 4) t[3] = (int32_t)low3[i];
+  counts[rank] = (int64_t)(kLowMax - (uint32_t)w);
 }
 
 uint32_t blocks_for(uint64_t n, uint64_t per) { return (uint32_t)((n + per - 1) / per); }
@@ -1531,19 +1594,18 @@ hipError_t scan_u32(const uint32_t* in, uint32_t* out, uint64_t n, uint32_t* par
 
 // Stable LSD sort of n keys (and payloads) by their low `bits` bits.  hist
 // holds kBins x ceil(n / tile) entries.
-template <bool PAIRS>
-hipError_t radix_sort(uint64_t*& keys, uint64_t*& keys_alt, uint64_t*& vals, uint64_t*& vals_alt,
-                      uint64_t n, int bits, uint32_t* hist, uint32_t* part, hipStream_t s) {
-  using K = uint64_t;
-  constexpr int ITEMS = tile_items<K, PAIRS, K>();
-  constexpr int TILE = tile_keys<K, PAIRS, K>();
+template <bool PAIRS, class K, class V>
+hipError_t radix_sort(K*& keys, K*& keys_alt, V*& vals, V*& vals_alt, uint64_t n, int bits,
+                      uint32_t* hist, uint32_t* part, hipStream_t s) {
+  constexpr int ITEMS = tile_items<K, PAIRS, V>();
+  constexpr int TILE = tile_keys<K, PAIRS, V>();
   const uint32_t ntiles = blocks_for(n, TILE);
   for (int shift = 0; shift < bits; shift += kDigitBits) {
     hipLaunchKernelGGL((k_rs_hist<K, TILE>), dim3(ntiles), dim3(kHistThreads), 0, s, keys, n, shift,
                        hist, ntiles);
     const hipError_t e = scan_u32(hist, hist, (uint64_t)kBins * ntiles, part, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_rs_scatter<K, K, PAIRS, ITEMS>), dim3(ntiles), dim3(kTileThreads), 0, s,
+    hipLaunchKernelGGL((k_rs_scatter<K, V, PAIRS, ITEMS>), dim3(ntiles), dim3(kTileThreads), 0, s,
                        keys, vals, n, shift, hist, ntiles, keys_alt, vals_alt);
     std::swap(keys, keys_alt);
     if (PAIRS) std::swap(vals, vals_alt);
@@ -1715,49 +1777,65 @@ tfe_status ngram_top_n(const int32_t* tokens, uint64_t nwin, int32_t vocab, uint
     BUILD_HIP(hipStreamSynchronize(s), "sync");
     if (nrec < ranks) return fail(TFE_ERR_HIP, "tie selection");
   }
-  R* rec = sc.get<R>(nrec);
-  R* rec2 = sc.get<R>(nrec);
-  if (!rec || !rec2) return fail(TFE_ERR_OOM, "rank arrays");
-  hipLaunchKernelGGL(k_gather<NG>, dim3(walkers), dim3(1024), 0, s, u, ts.pbits, tie ? 1u : 0u, rec,
-                     (uint32_t)nrec);
-  BUILD_HIP(hipGetLastError(), "record launches");
-  // 5. Ranks [skip, ranks).
-  const uint64_t m = ranks - skip;
-  if (nrec <= kBucketCap / 2) {
-    hipLaunchKernelGGL(k_bk_sort<R>, dim3(1), dim3(1024), 0, s, a, rec, (uint32_t)nrec, skip, ranks,
-                       NG, out_tuples, out_counts);
-  } else if (nrec <= bucket_sort_max<R>()) {
+  // 5. Ranks [skip, ranks).  The remainders and their counts are not needed
+  // once gathered: their arrays (nwin >= nrec entries each) are the ranking's
+  // scratch.  Ranks of n records from rank 0 on by the bucket sort:
+  auto rank_records = [&](R* rec, R* rec2, uint64_t n) {
+    if (n <= kBucketCap / 2) {
+      hipLaunchKernelGGL(k_bk_sort<R>, dim3(1), dim3(1024), 0, s, a, rec, (uint32_t)n, skip, ranks,
+                         NG, out_tuples, out_counts);
+      return;
+    }
     uint32_t nb = 2;
-    while (nb < max_buckets<R>() && nrec / nb > kBucketMean) nb <<= 1;
-    // The remainders and their counts are no longer needed: their arrays
-    // hold the splitters and every record's bucket.
-    R* split = sc.get<R>(nb);
-    uint16_t* bkt = sc.get<uint16_t>(nrec);
-    if (!split || !bkt) return fail(TFE_ERR_OOM, "rank arrays");
-    const uint32_t tiles = blocks_for(nrec, kBkTile);
-    hipLaunchKernelGGL(k_bk_sample<R>, dim3(1), dim3(1024), 0, s, rec, nrec, nb, split);
-    hipLaunchKernelGGL(k_bk_hist<R>, dim3(tiles), dim3(1024), 0, s, a, rec, nrec, nb, split, bkt);
-    hipLaunchKernelGGL(k_bk_scatter<R>, dim3(tiles), dim3(1024), 0, s, a, rec, nrec, nb, bkt, rec2);
+    while (nb < kMaxBuckets && n / nb > kBucketMean) nb <<= 1;
+    R* split = (R*)mcnt;  // fewer than n / 512 + 2 of at most 16 bytes
+    uint16_t* bkt = (uint16_t*)ucnt;
+    const uint32_t tiles = blocks_for(n, kBkTile);
+    hipLaunchKernelGGL(k_bk_sample<R>, dim3(1), dim3(1024), 0, s, rec, n, nb, split);
+    hipLaunchKernelGGL(k_bk_hist<R>, dim3(tiles), dim3(1024), 0, s, a, rec, n, nb, split, bkt);
+    hipLaunchKernelGGL(k_bk_scatter<R>, dim3(tiles), dim3(1024), 0, s, a, rec, n, nb, bkt, rec2);
     hipLaunchKernelGGL(k_bk_sort<R>, dim3(nb), dim3(1024), 0, s, a, rec2, 0u, skip, ranks, NG,
                        out_tuples, out_counts);
+  };
+  const uint64_t m = ranks - skip;
+  if (NG == 1 || nrec <= kBucketSortMax) {
+    R* rec = sc.get<R>(nrec);
+    R* rec2 = sc.get<R>(nrec);
+    if (!rec || !rec2) return fail(TFE_ERR_OOM, "rank arrays");
+    hipLaunchKernelGGL(k_gather<NG>, dim3(walkers), dim3(1024), 0, s, u, ts.pbits, tie ? 1u : 0u,
+                       rec, (uint32_t)nrec);
+    rank_records(rec, rec2, nrec);
   } else {
-    uint64_t *hi = (uint64_t*)rec, *hi2 = (uint64_t*)rec2, *lo = nullptr, *lo2 = nullptr;
-    uint32_t* rhist = sc.get<uint32_t>((uint64_t)kBins * blocks_for(nrec, kTileThreads * 6));
-    if (!rhist) return fail(TFE_ERR_OOM, "rank arrays");
-    if (sizeof(R) == 16) {
-      hi = sc.get<uint64_t>(nrec);
-      lo = sc.get<uint64_t>(nrec);
-      if (!hi || !lo) return fail(TFE_ERR_OOM, "rank arrays");
-      hipLaunchKernelGGL(k_split_rec2, dim3(blocks_for(nrec, 256)), dim3(256), 0, s, (const Rec2*)rec,
-                         nrec, hi, lo);
-      lo2 = hi2 + nrec;  // rec2's bytes hold both spare arrays
-      BUILD_HIP(radix_sort<true>(lo, lo2, hi, hi2, nrec, 36, rhist, part, s), "rank sort");
-      BUILD_HIP(radix_sort<true>(hi, hi2, lo, lo2, nrec, 64, rhist, part, s), "rank sort");
+    // At most nwin / (kLowMax + 1) n-grams are above kLowMax (and c* is not: more
+    // n-grams reach it).
+    const uint64_t nhigh = st[kStHigh], nlow = nrec - nhigh;
+    R* rec = sc.get<R>(nhigh);
+    R* rec2 = sc.get<R>(nhigh);
+    uint64_t* low = sc.get<uint64_t>(nlow);
+    uint64_t* low_alt = sizeof(K) == 8 ? (uint64_t*)ukey : sc.get<uint64_t>(nlow);
+    uint32_t* low3 = NG == 4 ? sc.get<uint32_t>(nlow) : nullptr;
+    uint32_t* low3_alt = ucnt;
+    if (!rec || !rec2 || !low || !low_alt || (NG == 4 && !low3))
+      return fail(TFE_ERR_OOM, "rank arrays");
+    hipLaunchKernelGGL(k_gather_long<NG>, dim3(walkers), dim3(1024), 0, s, u, ts.pbits, tie ? 1u : 0u,
+                       rec, (uint32_t)nhigh, low, low3, (uint32_t)nlow);
+    if (nhigh > skip) rank_records(rec, rec2, nhigh);
+    // Histograms of kBins words per tile of at least 3072 records: below 4 bytes
+    // a record.
+    static_assert(kBins < tile_keys<uint64_t, true, uint32_t>(), "mcnt holds the histograms");
+    if (NG == 4) {
+      BUILD_HIP(radix_sort<true>(low3, low3_alt, low, low_alt, nlow, 18, mcnt, part, s), "rank sort");
+      BUILD_HIP(radix_sort<true>(low, low_alt, low3, low3_alt, nlow, packed_tokens<NG>() + 9, mcnt,
+                                 part, s),
+                "rank sort");
     } else {
-      BUILD_HIP(radix_sort<false>(hi, hi2, lo, lo2, nrec, 64, rhist, part, s), "rank sort");
+      BUILD_HIP(radix_sort<false>(low, low_alt, low3, low3_alt, nlow, packed_tokens<NG>() + 9, mcnt,
+                                  part, s),
+                "rank sort");
     }
-    hipLaunchKernelGGL(k_unpack, dim3(blocks_for(m, 256)), dim3(256), 0, s, hi, lo, skip, m, NG,
-                       out_tuples, out_counts);
+    const uint64_t from = skip > nhigh ? skip - nhigh : 0, to = ranks - nhigh;
+    hipLaunchKernelGGL(k_unpack<NG>, dim3(blocks_for(to - from, 256)), dim3(256), 0, s, low, low3, from,
+                       to, nhigh, skip, out_tuples, out_counts);
   }
   BUILD_HIP(hipGetLastError(), "rank launches");
   BUILD_HIP(hipStreamSynchronize(s), "sync");

@@ -1,7 +1,12 @@
-"""GPU parity of every branch of tfe_ngram_top against the oracle (tuples and
-counts bit-exact): partitions counted in one slice and in several, count
-tables that fill up and are retried on parts of the remainders, the tie
-selection, and the three rankings (one bucket, bucket sort, radix sort)."""
+"""GPU parity of the branches of tfe_ngram_top against the oracle (tuples and
+counts bit-exact): partitions counted in one slice and in several, the tie
+selection, and the three rankings (one bucket, bucket sort, radix sort of packed
+records with the largest counts apart); count tables that fill up are in
+test_gpu_build_tables.py.  Not reached: a bucket larger than LDS holds, which no
+choice of input makes (it is sorted by the same function as the others, in
+memory)."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -10,7 +15,7 @@ import oracle
 from paper_2607_07388_amd import tfe
 
 from . import harness as H
-from .test_gpu_build import check
+from .test_gpu_build import check, gpu_top
 
 pytestmark = pytest.mark.gpu
 
@@ -20,18 +25,23 @@ def uniform(seed, N, vocab):
 
 
 @pytest.mark.parametrize("n,N,vocab,skip,top", [
-    # Up to 512 partitions of 11700 windows, nearly all distinct: 2-grams fill three
-    # quarters of a table, 3- and 4-grams (8192 entries) overflow it and retry.
+    # Tables at two thirds to three quarters of their entries: 512 partitions of 11700
+    # windows for 2-grams (16384 entries), 1024 of 5500 for 3- and 4-grams (8192).
     (2, 6000000, 1 << 18, 0, 3000),
     (3, 5600000, 1 << 18, 0, 3000),
     (4, 5600000, 1 << 18, 7, 3000),
-    # Every window asked for: the bucket sort, then records beyond it.
+    # Every window asked for: the bucket sort (2^20 records), then records beyond it.
+    (2, 1040000, 1 << 18, 0, 1040000),
+    (3, 900000, 1 << 17, 100, 900000),
+    (4, 600000, 1 << 18, 0, 600000),
     (3, 1500000, 1 << 17, 100, 1500000),
     (2, 9000000, 1 << 18, 5, 9000000),
     (4, 4600000, 1 << 18, 5, 4600000),
-    # Few ranks wanted of many equal counts: the tie selection (about 2^21 windows seen once).
+    # More equal counts than n-grams of one token can have, ranked with the rest.
     (1, 500000, 1 << 18, 0, 100),
+    # Few ranks wanted of many equal counts: the tie selection (about 2^21 windows seen once).
     (2, 2200000, 1 << 18, 0, 2000),
+    (3, 2200000, 1 << 18, 0, 100000),
     (4, 2200000, 1 << 18, 3, 2000),
 ])
 def test_uniform_streams(n, N, vocab, skip, top):
@@ -55,6 +65,71 @@ def test_ties_that_share_their_oldest_tokens(n, prefix, first):
     extra = w[rng.permutation(len(w))[:1000]]  # and some above the ties
     tok = np.concatenate([w, extra, extra]).ravel()
     check(tok, 1 << 18, n, 5, 3000)
+
+
+@pytest.mark.parametrize("n,vocab", [(1, 1 << 18), (2, 490)])
+def test_more_than_2_26_windows(n, vocab):
+    """4096 partitions of 1- and 2-grams, whose counts numpy adds up."""
+    tok = uniform(31 + n, (1 << 26) + 5000000, vocab)
+    key = tok if n == 1 else tok[:-1] * np.int32(vocab) + tok[1:]
+    counts = np.bincount(key, minlength=vocab ** n)
+    order = np.lexsort((np.arange(counts.size), -counts))[7:200007]
+    t, c = gpu_top(tok, vocab, n, 7, 200000)
+    np.testing.assert_array_equal(c, counts[order])
+    np.testing.assert_array_equal(t if n == 2 else t[:, 0],
+                                  np.stack([order // vocab, order % vocab], 1) if n == 2 else order)
+    tfe.tfe_ngram_release()
+
+
+@pytest.mark.parametrize("n", [2, 4])
+@pytest.mark.parametrize("count", [1, 2, 4095, 4096, 4097, 8193, 1 << 20, (1 << 20) + 1])
+def test_rankings_at_their_limits(n, count):
+    """That many n-grams, each seen once (windows broken apart by -1): ranked in
+    tuple order by one bucket (up to 4096), the bucket sort (2^20), the radix sort."""
+    rng = np.random.default_rng(count + n)
+    key = rng.permutation(np.unique(rng.integers(0, 1 << 36, count + 1000))[:count])
+    w = np.full((count, n + 1), 9, np.int32)
+    w[:, 0], w[:, n - 1], w[:, n] = key >> 18, key & ((1 << 18) - 1), -1
+    t, c = gpu_top(w.ravel(), 1 << 18, n, 0, count + 5)
+    assert c.size == count and np.all(c == 1)
+    np.testing.assert_array_equal(t, w[np.argsort(key), :n])
+
+
+def test_rankings_of_millions_take_even_time():
+    """The ranking does not depend on how lucky a sample is: of 100 calls that
+    rank 4.18M 3-grams, the fourth slowest takes at most 2.5 times the fastest."""
+    N = 4180000
+    tok = torch.from_numpy(uniform(41, N, 1 << 18)).cuda()
+    tup = torch.empty((N, 3), dtype=torch.int32, device="cuda")
+    cnt = torch.empty(N, dtype=torch.int64, device="cuda")
+    took = []
+    for _ in range(101):
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        tfe.tfe_ngram_top(tok, N, 1 << 18, 3, 0, N, tup, cnt, H.cur_stream())
+        took.append(time.perf_counter() - t0)
+    took = sorted(took[1:])
+    assert took[-4] < 2.5 * took[0], took
+
+
+@pytest.mark.parametrize("n,often", [(2, 5000), (3, 30), (4, 5000)])
+def test_long_rankings_with_large_counts(n, often):
+    """More than 2^20 ranks, of which those with counts above 511 are ranked apart
+    (often = 5000: by the bucket sort)."""
+    rng = np.random.default_rng(often + n)
+    w = rng.integers(0, 1 << 18, (1200000 + often, n + 1)).astype(np.int32)
+    w[:, n] = -1
+    copies = 1 + (rng.random(len(w)) < 0.05).astype(np.int64) * rng.integers(0, 4, len(w))
+    copies[:often] = rng.integers(508, 516, often)
+    copies[:5] = [511, 512, 513, 600, 1000]
+    tok = np.repeat(w, copies, axis=0).ravel()
+    high = int((copies > 511).sum())
+    want_t, want_c = oracle.ngram_top(tok, 1 << 18, n, 0, len(w))
+    assert (want_c > 511).sum() == high and len(want_c) > (1 << 20)
+    for skip, top in [(0, len(w)), (high - 3, 1150000), (high, 1150000), (high + 7, 1150000), (3, 1150000)]:
+        t, c = gpu_top(tok, 1 << 18, n, skip, top)
+        np.testing.assert_array_equal(t, want_t[skip:skip + top])
+        np.testing.assert_array_equal(c, want_c[skip:skip + top])
 
 
 @pytest.mark.parametrize("n", [1, 2, 3, 4])
