@@ -33,7 +33,8 @@ struct HeadArgs {
   uint64_t* cand;       // [64 x nblk x ccap]
   unsigned long long* bar;
   unsigned long long* fault;  // number of the last call that gave up
-  unsigned long long* ncall;  // two-launch calls on this head so far (may be null)
+  unsigned long long* ncall;  // two-launch calls on this head so far that fit one launch
+                              // (null: this one does not)
   uint32_t ccap;        // 1 + 16 x the most tiles a block owns, rounded up to 16
   unsigned long long* ectl;  // [16 i], i < 16: blocks of earlier one-launch calls
                              // on this scratch that have left (block b adds to b mod 16)

@@ -624,7 +624,7 @@ __global__ __launch_bounds__(kRowThreads) void k_head_rows(const HeadArgs a) {
     s_ntile = 0;
     s_nc = 0;
     s_lo = 0;
-    // One more two-launch call of the head.
+    // One more two-launch call of the head that fits one launch.
     if (b == 0 && a.ncall)
       (void)__hip_atomic_fetch_add(a.ncall, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
@@ -964,7 +964,8 @@ __device__ __forceinline__ uint64_t call_epoch(const HeadArgs& a) {
   return n / a.nblk;
 }
 
-// The number of the call with one-launch epoch e among the head's calls.
+// The number of the call with one-launch epoch e among the head's calls that
+// fit one launch.
 __device__ __forceinline__ unsigned long long call_number(const HeadArgs& a, uint64_t e) {
   return __hip_atomic_load(a.ncall, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + e + 1ull;
 }

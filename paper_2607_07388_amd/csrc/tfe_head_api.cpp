@@ -257,8 +257,9 @@ tfe_status topk(tfe_head* h, const void* hidden, int32_t B, int32_t K, int32_t* 
   HEAD_HIP(hipStreamIsCapturing(stream, &cs), "hipStreamIsCapturing");
   if (h->fused) fuse_args(h, &a);
   const char* wl = getenv("TFE_HEAD_WAIT_LIMIT");
-  const bool one = h->fused && h->device < kOrderDevices && head_fused_fits(a) &&
-                   (wl || head_fused_faster(a));
+  const bool fits = h->fused && h->device < kOrderDevices && head_fused_fits(a);
+  const bool one = fits && (wl || head_fused_faster(a));
+  if (!fits) a.ncall = nullptr;  // not numbered: such a call never gives up
   a.wait_limit = wl ? (uint32_t)strtoul(wl, nullptr, 0) : kHeadWaitLimit;
   auto launch = [&] {
     if (one) return launch_head_fused(a, stream);

@@ -50,6 +50,36 @@ def test_one_launch_heavy_ties(monkeypatch):
         tfe.tfe_head_free(head)
 
 
+def test_faults_are_numbered_over_the_calls_that_fit_one_launch(monkeypatch):
+    """Calls of at most 64 rows count, by whichever route; larger ones do not
+    (they never took one launch)."""
+    V, D, B, K = 9000, 256, 100, 16
+    w, h = gaussian(33, V, D, B)
+    head = tfe.tfe_head_create(w, V, D, B, K)
+
+    def gives_up(rows):
+        monkeypatch.setenv("TFE_HEAD_WAIT_LIMIT", "0")
+        ids, prob = one_launch(head, h, rows, K)
+        monkeypatch.delenv("TFE_HEAD_WAIT_LIMIT")
+        return np.all(ids == -1) and np.all(prob == 0)
+
+    try:
+        want = one_launch(head, h, B, K)[0]                     # two launches, not counted
+        assert gives_up(8)                                      # 1
+        assert tfe.tfe_head_last_fault(head) == 1
+        for rows in (100, 65):
+            np.testing.assert_array_equal(one_launch(head, h, rows, K)[0], want[:rows])
+        assert tfe.tfe_head_last_fault(head) == 1
+        np.testing.assert_array_equal(one_launch(head, h, 8, K)[0], want[:8])  # 2: two launches
+        one_launch(head, h, 70, K)
+        assert gives_up(64)                                     # 3
+        assert tfe.tfe_head_last_fault(head) == 3
+        assert not gives_up(100)                                # never one launch
+        assert tfe.tfe_head_last_fault(head) == 3
+    finally:
+        tfe.tfe_head_free(head)
+
+
 def test_calls_of_one_head_on_two_streams(monkeypatch):
     """Calls of one head alternate between two streams without
     synchronisation; each waits on the device for the one before."""
