@@ -283,11 +283,12 @@ tfe_status tfe_head_create(const void *w_pref, int32_t vocab, int32_t dim, int32
  * synchronised).
  * A call takes two launches (logits, then the per-row selection), also under
  * stream capture; on another stream than the head's previous call it waits on
- * the device for that call.  Calls of 17 to 64 rows over 2^17 tokens or more
- * with K at most the number of compute units (a power of two up to 256; at
- * most 48 16-token tiles per compute unit) take a one-launch path, as does
- * every call of at most 64 rows with such a K while the environment variable
- * TFE_HEAD_WAIT_LIMIT is set: one block per compute unit keeps its logits in
+ * the device for that call.  Calls of at most 64 rows with K at most the
+ * number of compute units (a power of two up to 256; at most 48 16-token tiles
+ * per compute unit) fit a one-launch path, which is taken where it is faster
+ * (vocabularies of 98304 tokens or more, depending on rows, K and dim), and by
+ * every such call while the environment variable TFE_HEAD_WAIT_LIMIT is set:
+ * one block per compute unit keeps its logits in
  * registers, and two device-wide barriers
  * inside the launch replace the write of the logits.  Its blocks must all
  * be resident at once: the library runs the one-launch calls of all heads

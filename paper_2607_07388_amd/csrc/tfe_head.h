@@ -60,14 +60,17 @@ hipError_t launch_head_rows(const HeadArgs& a, hipStream_t s);
 // B and K at most nblk, nblk a power of two <= 256, at most 48 tiles per
 // block).
 bool head_fused_fits(const HeadArgs& a);
-// True where one launch is the faster way for a call that fits it: many rows
-// and a large vocabulary, so that the logits' write outweighs the two grid
-// barriers.  Two launches / one, us, at dim 1024 with rotating projections:
-//   151936 tokens: 64 rows, K = 128: 78.4 / 74.2; 32 rows, K = 64: 71.1 / 69.9;
-//                  16 rows, K = 64: 65.4 / 69.3; one row 64 / 68
-//   120000 tokens: 66.1 / 67.6; 59.7 / 63.4; 57.0 / 61.6
-//    50000 tokens: 64 rows 38.8 / 46.1, one row 31.3 / 38.9
-// (dim 256, 151936 tokens: 41.5 / 39.8; 34.7 / 35.5; 31.4 / 34.9).
+// True where one launch is the faster way for a call that fits it.  Two
+// launches / one, us a call (medians of calls in turn, rotating projections):
+//   K above 128: the two-launch bound from the blocks' maxima passes many tiles.
+//     K = 192, 17 rows: dim 256 34.5 / 34.5 at 80000 tokens, 39.5 / 36.6 at 100000, 45.5 / 40.3 at
+//     151936; dim 1024 63.9 / 64.5 at 100000, 74.4 / 69.6 at 128256, 79.0 / 73.7 at 151936.
+//     K = 256, 64 rows: dim 256 43.3 / 44.2 at 100000, 44.2 / 47.0 at 110000, 49.3 / 48.7 at 140000.
+//   Else many rows and a large vocabulary, so that the logits' write outweighs
+//     the two grid barriers.  64 rows, K = 64: dim 256 34.1 / 35.1 at 120000, 37.2 / 36.3 at
+//     140000, 42.4 / 38.1 at 170000; dim 1024 68.3 / 68.3 at 140000, 79.8 / 76.2 at 170000.  17 rows:
+//     dim 256 32.9 / 33.0 at 140000, 34.6 / 34.0 at 151936.  One row: dim 1024 64.4 / 64.9 at 151936,
+//     77.0 / 74.8 at 190000; dim 256 31.2 / 32.3 at 151936.
 bool head_fused_faster(const HeadArgs& a);
 // Words per (row, block) segment of the candidate scratch for this vocabulary.
 uint32_t head_fused_ccap(uint32_t V, uint32_t nblk);

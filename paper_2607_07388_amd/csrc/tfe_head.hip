@@ -16,9 +16,9 @@
 //                  K tiles (every top-K logit lies in one of the K tiles with
 //                  the largest maxima, equal maxima taken in tile order), then
 //                  those tiles' logits ranked in LDS.
-// For up to 64 rows, K at most the number of compute units and a large
-// vocabulary (head_fused_faster has both sides measured), one launch:
-// k_head_fused (below, with its design).
+// For up to 64 rows and K at most the number of compute units, where it is
+// faster (head_fused_faster has both sides measured), one launch: k_head_fused
+// (below, with its design).
 // Ties in logit go to the lower token id, so the answer is unique.  The K
 // output probabilities use the full-accuracy expf (about 1 ulp); the chunk
 // sums of exp(l - max) use the hardware exponential, whose relative error
@@ -40,14 +40,11 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-#ifndef TFE_HEAD_WAVES
-#define TFE_HEAD_WAVES 8
-#endif
 #ifndef TFE_HEAD_NT
 #define TFE_HEAD_NT 1
 #endif
 
-constexpr int kLogitWaves = TFE_HEAD_WAVES;  // waves per logits block (tuning knob)
+constexpr int kLogitWaves = 8;   // waves per logits block
 constexpr int kCols = 64;        // hidden rows per logits block (4 MFMA column tiles)
 
 // Order-preserving float -> uint32 map (larger float, larger key).
@@ -536,35 +533,89 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
   return x + (row >= 1 ? r0 : 0u) + (row >= 2 ? r1 : 0u) + (row >= 3 ? r2 : 0u);
 }
 
-// Bitonic sort of a[0, N2) in LDS, descending; N2 a power of two.
-template <int NT>
-__device__ void lds_sort_desc(uint64_t* a, uint32_t N2) {
-  for (uint32_t size = 2; size <= N2; size <<= 1) {
-    for (uint32_t stride = size >> 1; stride > 0; stride >>= 1) {
-      for (uint32_t e = threadIdx.x; e < N2 / 2; e += NT) {
-        const uint32_t i = 2 * e - (e & (stride - 1));
-        const uint32_t j = i + stride;
-        const bool desc = (i & size) == 0;
-        const uint64_t x = a[i], y = a[j];
-        if ((x < y) == desc) {
-          a[i] = y;
-          a[j] = x;
-        }
+// Wave 0 finds the histogram bin that holds the need-th largest key (lane l
+// holds bins 255 - 4 l - k, k = 0..3, in descending order) and leaves the
+// bin, the count above it and its own count in s_sel[0..2].
+__device__ __forceinline__ void pick_bin(const uint32_t* hist, uint32_t need, uint32_t* s_sel) {
+  const int lane = threadIdx.x & 63;
+  uint32_t v[4], sum = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    v[k] = hist[255 - 4 * lane - k];
+    sum += v[k];
+  }
+  const uint32_t inc = wave_incl_scan(sum);
+  uint32_t ex = inc - sum;
+  if (ex < need && need <= inc) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (ex < need && need <= ex + v[k]) {
+        s_sel[0] = 255u - 4u * (uint32_t)lane - (uint32_t)k;
+        s_sel[1] = ex;
+        s_sel[2] = v[k];
       }
-      __syncthreads();
+      ex += v[k];
     }
   }
 }
 
-__device__ __forceinline__ uint32_t pow2_ceil(uint32_t x) {
-  uint32_t p = 1;
-  while (p < x) p <<= 1;
-  return p;
+// Adds a key to the radix histogram of the current pass if it agrees with
+// the decided bits (lanes holding the first active lane's digit add their
+// number with one atomic).
+__device__ __forceinline__ void hist_key(uint32_t* hist, bool in, uint64_t key, uint64_t dm,
+                                         uint64_t lo, int sh) {
+  in = in && (key & dm) == lo;
+  const uint64_t act = __builtin_amdgcn_ballot_w64(in);
+  if (!act) return;
+  const uint32_t d = (uint32_t)(key >> sh) & 255u;
+  const int first = __builtin_ctzll(act);
+  const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, first);
+  const uint64_t same = __builtin_amdgcn_ballot_w64(in && d == d0);
+  const int lane = threadIdx.x & 63;
+  if (in && d != d0) atomicAdd(&hist[d], 1u);
+  else if (lane == first) atomicAdd(&hist[d0], (uint32_t)__builtin_popcountll(same));
+}
+
+// A lower bound of the `need`-th largest of the n keys in LDS, of which those
+// at or above it are exactly the need largest (keys are distinct, all in
+// [kmin, kmax]): a radix select, 8-bit digits from the highest bit in which kmin
+// and kmax differ, by NT threads.
+template <int NT>
+__device__ __forceinline__ uint64_t select_lds(const uint64_t* c, uint32_t n, uint32_t need,
+                                               uint64_t kmin, uint64_t kmax, uint32_t* hist,
+                                               uint32_t* s_sel) {
+  const uint32_t tid = threadIdx.x;
+  const uint64_t dk = kmax ^ kmin;
+  const int top = dk ? 63 - __builtin_clzll(dk) : 0;
+  const int sh0 = max(top - 7, 0);
+  uint64_t dm = sh0 + 8 < 64 ? ~((1ull << (sh0 + 8)) - 1ull) : 0ull;
+  uint64_t lo = kmax & dm;
+  for (int sh = sh0;; sh = max(sh - 8, 0)) {
+    if (tid < 256) hist[tid] = 0u;
+    __syncthreads();
+    for (uint32_t e0 = 0; e0 < n; e0 += NT) {
+      const uint32_t e = e0 + tid;
+      hist_key(hist, e < n, e < n ? c[e] : 0ull, dm, lo, sh);
+    }
+    __syncthreads();
+    if (tid < 64) pick_bin(hist, need, s_sel);
+    __syncthreads();
+    const uint32_t bin = s_sel[0], ab = s_sel[1], cb = s_sel[2];
+    need -= ab;
+    lo |= (uint64_t)bin << sh;
+    dm |= 0xFFull << sh;
+    __syncthreads();  // s_sel is read by every thread before it is written again
+    if (cb == need || sh == 0) return lo;
+  }
 }
 
 constexpr int kRowThreads = 1024;
 constexpr int kRowTiles = kHeadMaxTiles / kRowThreads;  // tile entries per thread
 constexpr int kRowCand = 16 * kHeadMaxK;                // logits of the candidate tiles
+// Candidates ranked outright (dim 256, V = 1000, K = 64, where all logits are
+// candidates: 33.2 us a call, 16.7 with the select; 4000, K = 256: 49.8 with the
+// bitonic sort that ranked more than 1024, now 23.9).
+constexpr uint32_t kRowCount = 512;
 
 // Appends the tiles whose masked key reaches lo ((key & msk) >= lo) to
 // s_tiles, in no particular order (the ranking does not depend on it): each
@@ -602,15 +653,15 @@ __device__ __forceinline__ void list_tiles(const uint64_t (&key)[NI], uint32_t N
 //      hold at most 192 tiles (or exactly K).  The K tiles with the largest
 //      maxima are among them and hold every top-K logit, and every top-K
 //      logit is at or above the bins' lower bound.
-//   3. The logits of those tiles at or above that bound are ranked in LDS,
-//      by counting when there are at most 1024 of them, else by a bitonic
-//      sort; the first K are the answer.  The tile and logit lists are
+//   3. The logits of those tiles at or above that bound are ranked in LDS
+//      by counting (when there are many of them, the K largest, which a radix
+//      select finds first); the first K are the answer.  The tile and logit lists are
 //      built with wave-aggregated LDS appends in no particular order (the
 //      ranking does not depend on it; keys are distinct), which took the
 //      call from 87.5 to 81.9 us against block-wide scans per round.
 __global__ __launch_bounds__(kRowThreads) void k_head_rows(const HeadArgs a) {
-  __shared__ uint64_t s_cand[kRowCand];
-  __shared__ uint32_t hist[256];
+  __shared__ uint64_t s_cand[kRowCand], s_top[kHeadMaxK];
+  __shared__ uint32_t hist[256], s_sel[3];
   __shared__ uint32_t s_tiles[kHeadMaxK];
   __shared__ uint32_t s_wave[kRowThreads / 64];
   __shared__ uint32_t s_wmin[kRowThreads / 64];
@@ -870,25 +921,40 @@ __global__ __launch_bounds__(kRowThreads) void k_head_rows(const HeadArgs a) {
     a.top_ids[(size_t)b * a.K + i] = (int32_t)(0xFFFFFFFFu - (uint32_t)k);
     a.top_prob[(size_t)b * a.K + i] = expf(key2f((uint32_t)(k >> 32)) - M) * invS;
   };
-  if (n_c <= (uint32_t)kRowThreads) {
-    // Usually a little over K candidates: each thread ranks its own by
-    // counting the larger ones (keys are distinct; every thread reads the
-    // same LDS word at a time), with no sorting network.
-    if ((uint32_t)tid < n_c) {
-      const uint64_t k = s_cand[tid];
-      uint32_t rank = 0;
-      for (uint32_t u = 0; u < n_c; ++u) rank += s_cand[u] > k ? 1u : 0u;
-      if (rank < a.K) emit(rank, k);
+  // Usually a little over K candidates: each thread ranks its own by counting
+  // the larger ones (keys are distinct; every thread reads the same LDS word at a
+  // time), with no sorting network.  Of many (K near the number of tiles, or
+  // more) the K largest are selected first.
+  auto rank_all = [&](const uint64_t* k, uint32_t n) {
+    if ((uint32_t)tid >= n) return;
+    const uint64_t x = k[tid];
+    uint32_t rank = 0;
+    for (uint32_t u = 0; u < n; ++u) rank += k[u] > x ? 1u : 0u;
+    if (rank < a.K) emit(rank, x);
+  };
+  if (n_c <= kRowCount) {  // block-uniform
+    rank_all(s_cand, n_c);
+  } else {
+    const uint64_t lo = select_lds<kRowThreads>(s_cand, n_c, a.K, tau,
+                                                ((uint64_t)hmax << 32) | 0xFFFFFFFFull, hist, s_sel);
+    if (tid == 0) s_nc = 0;
+    __syncthreads();
+    for (uint32_t e0 = 0; e0 < n_c; e0 += kRowThreads) {
+      const uint32_t e = e0 + tid;
+      const uint64_t k = e < n_c ? s_cand[e] : 0ull;
+      const bool in = e < n_c && k >= lo;
+      const uint64_t m = __builtin_amdgcn_ballot_w64(in);
+      if (m) {
+        uint32_t o = 0;
+        if (lane == 0) o = atomicAdd(&s_nc, (uint32_t)__builtin_popcountll(m));
+        o = __builtin_amdgcn_readfirstlane(o) + (uint32_t)__builtin_popcountll(m & below);
+        if (in && o < (uint32_t)kHeadMaxK) s_top[o] = k;
+      }
     }
-    return;
+    __syncthreads();
+    rank_all(s_top, min(s_nc, (uint32_t)kHeadMaxK));
   }
-  const uint32_t N2 = pow2_ceil(n_c);
-  for (uint32_t e = n_c + tid; e < N2; e += kRowThreads) s_cand[e] = 0;
-  __syncthreads();
-  lds_sort_desc<kRowThreads>(s_cand, N2);
-  for (uint32_t i = tid; i < a.K; i += kRowThreads) emit(i, s_cand[i]);
 }
-
 
 // ---------------------------------------------------------------------------
 // One launch for up to 64 rows (K at most the number of blocks).
@@ -1048,49 +1114,6 @@ __device__ __forceinline__ void col_lse(float& m, float& s) {
   m = __uint_as_float(m32[0]);
   s = __uint_as_float(s32[0]);
   lse_merge(m, s, __uint_as_float(m32[1]), __uint_as_float(s32[1]));
-}
-
-// Wave 0 finds the histogram bin that holds the need-th largest key (lane l
-// holds bins 255 - 4 l - k, k = 0..3, in descending order) and leaves the
-// bin, the count above it and its own count in s_sel[0..2].
-__device__ __forceinline__ void pick_bin(const uint32_t* hist, uint32_t need, uint32_t* s_sel) {
-  const int lane = threadIdx.x & 63;
-  uint32_t v[4], sum = 0;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    v[k] = hist[255 - 4 * lane - k];
-    sum += v[k];
-  }
-  const uint32_t inc = wave_incl_scan(sum);
-  uint32_t ex = inc - sum;
-  if (ex < need && need <= inc) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      if (ex < need && need <= ex + v[k]) {
-        s_sel[0] = 255u - 4u * (uint32_t)lane - (uint32_t)k;
-        s_sel[1] = ex;
-        s_sel[2] = v[k];
-      }
-      ex += v[k];
-    }
-  }
-}
-
-// Adds a key to the radix histogram of the current pass if it agrees with
-// the decided bits (lanes holding the first active lane's digit add their
-// number with one atomic).
-__device__ __forceinline__ void hist_key(uint32_t* hist, bool in, uint64_t key, uint64_t dm,
-                                         uint64_t lo, int sh) {
-  in = in && (key & dm) == lo;
-  const uint64_t act = __builtin_amdgcn_ballot_w64(in);
-  if (!act) return;
-  const uint32_t d = (uint32_t)(key >> sh) & 255u;
-  const int first = __builtin_ctzll(act);
-  const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, first);
-  const uint64_t same = __builtin_amdgcn_ballot_w64(in && d == d0);
-  const int lane = threadIdx.x & 63;
-  if (in && d != d0) atomicAdd(&hist[d], 1u);
-  else if (lane == first) atomicAdd(&hist[d0], (uint32_t)__builtin_popcountll(same));
 }
 
 template <int KS>
@@ -1420,29 +1443,8 @@ __global__ __launch_bounds__(kFuseThreads) void k_head_fused(const HeadArgs a) {
   __syncthreads();
   // Exact K-th largest key of the nl >= K candidates in LDS: afterwards the
   // keys >= lo are exactly the K largest.
-  uint64_t lo = 0;
-  if (nl > K) {
-    lo = kmax & dm0;
-    uint64_t dm = dm0;
-    uint32_t need = K;
-    for (int sh = sh0;; sh = max(sh - 8, 0)) {
-      if (tid < 256) hist[tid] = 0u;
-      __syncthreads();
-      for (uint32_t e0 = 0; e0 < nl; e0 += kFuseThreads) {
-        const uint32_t e = e0 + tid;
-        hist_key(hist, e < nl, e < nl ? s_c[e] : 0ull, dm, lo, sh);
-      }
-      __syncthreads();
-      if (wave == 0) pick_bin(hist, need, s_sel);
-      __syncthreads();
-      const uint32_t bin = s_sel[0], ab = s_sel[1], cb = s_sel[2];
-      need -= ab;
-      lo |= (uint64_t)bin << sh;
-      dm |= 0xFFull << sh;
-      __syncthreads();
-      if (cb == need || sh == 0) break;
-    }
-  }
+  const uint64_t lo =
+      nl > K ? select_lds<kFuseThreads>(s_c, nl, K, kmin, kmax, hist, s_sel) : 0ull;
   const uint64_t below = (1ull << lane) - 1ull;
   for (uint32_t e0 = 0; e0 < nl; e0 += kFuseThreads) {
     const uint32_t e = e0 + tid;
@@ -1522,7 +1524,11 @@ bool head_fused_fits(const HeadArgs& a) {
   return (tiles + kTileGroup - 1) / kTileGroup <= (uint32_t)(kFuseGroups * kLogitWaves);
 }
 
-bool head_fused_faster(const HeadArgs& a) { return a.B > 16 && a.V >= (1u << 17); }
+bool head_fused_faster(const HeadArgs& a) {
+  if (a.K > 128) return a.V >= (a.D == 1024 ? 8u : a.K > 192 ? 7u : 6u) << 14;
+  if (a.B > 16) return a.V >= 9u << 14;
+  return a.D == 1024 && a.V >= 11u << 14;
+}
 
 bool head_fused_resident(int D) {
   const void* f = D == 256 ? (const void*)k_head_fused<8>

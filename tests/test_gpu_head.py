@@ -64,6 +64,11 @@ class Head:
     (40000, 1024, 100, 64),    # two column groups (64 + 36 rows), ten chunks
     (151936, 1024, 64, 128),   # the backbone vocabulary, one batch-64 decode step
     (1 << 18, 256, 3, 256),    # the largest vocabulary (16384 tiles) and the largest K
+    (512, 256, 4, 32),         # as many candidates as are ranked outright, all of the logits
+    (513, 256, 4, 33),         # one more: the K largest are selected first
+    (1000, 512, 3, 256),
+    (4080, 256, 70, 200),      # most tiles are candidates
+    (4096, 1024, 5, 256),      # all of them, 4096 logits
 ])
 def test_integer_logits_bit_exact_ids(V, D, B, K):
     w, h = int_inputs(V + D + B, V, D, B)
@@ -102,6 +107,17 @@ def test_wide_batches_bit_exact_ids(V, D, B, K):
     ids2, prob2 = head.topk(np.roll(h, 1, axis=0), K)
     np.testing.assert_array_equal(np.roll(ids2, -1, axis=0), ids)
     np.testing.assert_allclose(np.roll(prob2, -1, axis=0), prob, rtol=2e-6, atol=1e-36)
+    head.close()
+
+
+@pytest.mark.parametrize("V", [500, 700, 4096, 5000])
+def test_equal_logits(V):
+    """Ids decide alone: the K lowest, each with probability 1 / V."""
+    K = min(256, V)
+    head = Head(np.zeros((V, 256), np.uint16), 2, K)
+    ids, prob = head.topk(bf16_bits(np.ones((2, 256), np.float32)), K)
+    np.testing.assert_array_equal(ids, np.tile(np.arange(K, dtype=np.int32), (2, 1)))
+    np.testing.assert_allclose(prob, 1 / V, rtol=1e-5)
     head.close()
 
 

@@ -1,5 +1,6 @@
 """The one-launch head (tfe_head_topk for at most 64 rows and K at most the
-number of compute units: logits held in registers, a bound of each row's
+number of compute units, where it is faster or while TFE_HEAD_WAIT_LIMIT is
+set: logits held in registers, a bound of each row's
 K-th largest logit from the blocks' maxima, only the logits above it
 written) against the two-launch kernels (tfe_head_topk_noalloc, which
 writes every logit), on the same inputs: ids bit-exact and probabilities
@@ -15,7 +16,7 @@ two heads on two streams without synchronisation run one after another;
 calls captured in a HIP graph replay correctly between eager calls; a
 call
 whose barrier waits are forced to give up (TFE_HEAD_WAIT_LIMIT=0) answers
--1 and leaves the head working."""
+-1 and leaves the head working, by either route."""
 import numpy as np
 import pytest
 import torch
@@ -26,6 +27,15 @@ from paper_2607_07388_amd import tfe
 from . import harness as H
 
 pytestmark = pytest.mark.gpu
+
+
+WAIT = str(1 << 20)  # polls, about a second: the waits end long before
+
+
+@pytest.fixture
+def one_route(monkeypatch):
+    """Calls that fit one launch take it, at the usual limit."""
+    monkeypatch.setenv("TFE_HEAD_WAIT_LIMIT", WAIT)
 
 
 def two_launch(w, V, D, h, B, K):
@@ -85,11 +95,13 @@ def check(w, h, V, D, B, K, calls=1):
     (300, 512, 17, 256),       # fewer tiles than blocks: empty blocks
     (100, 1024, 64, 50),
 ])
+@pytest.mark.usefixtures("one_route")
 def test_gaussian(V, D, B, K):
     w, h = gaussian(V + K, V, D, B)
     check(w, h, V, D, B, K)
 
 
+@pytest.mark.usefixtures("one_route")
 def test_all_logits_equal_narrows_in_memory():
     V, D, B, K = 151936, 1024, 64, 128
     w = torch.zeros((V, D), dtype=torch.bfloat16, device="cuda")
@@ -97,6 +109,7 @@ def test_all_logits_equal_narrows_in_memory():
     check(w, h, V, D, B, K)
 
 
+@pytest.mark.usefixtures("one_route")
 def test_integer_ties():
     V, D, B = 151936, 256, 64
     w, h = small_ints(4, V, D, B, 0, 2)
@@ -105,6 +118,7 @@ def test_integer_ties():
     check(w, h, V, D, B, 256)
 
 
+@pytest.mark.usefixtures("one_route")
 def test_largest_logits_clustered_in_a_few_blocks():
     V, D, B, K = 151936, 1024, 64, 256
     w, h = gaussian(6, V, D, B)
@@ -234,25 +248,40 @@ def test_a_barrier_wait_that_gives_up_fails_only_its_call(monkeypatch):
     makes every wait give up at once (forced from the host: every block
     still arrives, so no kernel waits forever).  That call answers every row
     with id -1 and probability 0, and tfe_head_last_fault names it; the next
-    calls on the same head, with the default limit, are correct again (the
-    barrier counters stayed aligned) and leave the fault record as it was."""
+    calls on the same head, by one launch at the usual limit and by the two
+    launches in turn, are correct again (the barrier counters stayed aligned)
+    and leave the fault record as it was, until another call gives up."""
     V, D, B, K = 40000, 1024, 64, 64
     w, h = gaussian(11, V, D, B)
     want = two_launch(w, V, D, h, B, K)
     head = tfe.tfe_head_create(w, V, D, B, K)
     try:
-        ids, prob = one_launch(head, h, B, K)
-        np.testing.assert_array_equal(ids, want[0])
-        assert tfe.tfe_head_last_fault(head) == 0
-        monkeypatch.setenv("TFE_HEAD_WAIT_LIMIT", "0")
-        ids, prob = one_launch(head, h, B, K)
-        assert np.all(ids == -1) and np.all(prob == 0)
-        assert tfe.tfe_head_last_fault(head) == 2  # the second one-launch call
-        monkeypatch.delenv("TFE_HEAD_WAIT_LIMIT")
-        for _ in range(3):
+        def right(limit):
+            if limit is None:
+                monkeypatch.delenv("TFE_HEAD_WAIT_LIMIT")  # two launches for this vocabulary
+            else:
+                monkeypatch.setenv("TFE_HEAD_WAIT_LIMIT", limit)
             ids, prob = one_launch(head, h, B, K)
             np.testing.assert_array_equal(ids, want[0])
             np.testing.assert_allclose(prob, want[1], rtol=1e-5, atol=1e-37)
+
+        def gives_up():
+            monkeypatch.setenv("TFE_HEAD_WAIT_LIMIT", "0")
+            ids, prob = one_launch(head, h, B, K)
+            assert np.all(ids == -1) and np.all(prob == 0)
+
+        right(WAIT)
+        assert tfe.tfe_head_last_fault(head) == 0
+        gives_up()
+        assert tfe.tfe_head_last_fault(head) == 2  # the head's second call
+        for _ in range(3):
+            right(WAIT)
+        right(None)
+        right(WAIT)
         assert tfe.tfe_head_last_fault(head) == 2
+        gives_up()
+        assert tfe.tfe_head_last_fault(head) == 8
+        right(WAIT)
+        right(None)
     finally:
         tfe.tfe_head_free(head)
