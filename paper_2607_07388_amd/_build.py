@@ -21,13 +21,15 @@ HIP_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
 
 
 def build_calls():
+    # The output under a name of its own: ranks of one job may all build at once.
+    tmp = "%s.tmp%x" % (CALLS, os.getpid())
     cmd = ["g++", "-O3", "-std=c++17", "-shared", "-fPIC", "-Wall", "-fvisibility=hidden",
            "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "tfe_calls.cpp"),
-           "-o", CALLS + ".tmp"]
+           "-o", tmp]
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if r.returncode != 0:
         raise RuntimeError("_calls build failed: %s\n%s" % (" ".join(cmd), r.stdout))
-    os.replace(CALLS + ".tmp", CALLS)
+    os.replace(tmp, CALLS)
 
 
 def build(verbose=False):

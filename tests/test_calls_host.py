@@ -77,6 +77,31 @@ def test_other_forms_are_handed_on(recorder, args, kw):
     assert all(x is y for x, y in zip(handed[0][0], args))
 
 
+def test_processes_that_build_the_module_together(monkeypatch, tmp_path):
+    """Ranks that find no module all build it: one that finishes while another
+    is still compiling leaves that one's output alone."""
+    import subprocess
+
+    from paper_2607_07388_amd import _build
+    monkeypatch.setattr(_build, "CALLS", str(tmp_path / "_calls.so"))
+    run = subprocess.run
+    pid, depth = _build.os.getpid(), []
+
+    def compile_beside_another(*a, **k):
+        r = run(*a, **k)
+        if not depth:  # the other process starts later and ends first
+            depth.append(1)
+            monkeypatch.setattr(_build.os, "getpid", lambda: pid + 1)
+            _build.build_calls()
+            monkeypatch.setattr(_build.os, "getpid", lambda: pid)
+        return r
+
+    monkeypatch.setattr(_build.subprocess, "run", compile_beside_another)
+    _build.build_calls()
+    assert [p.name for p in tmp_path.iterdir()] == ["_calls.so"]
+    ctypes.PyDLL(str(tmp_path / "_calls.so")).PyInit__calls
+
+
 def test_negative_status_raises(recorder):
     with pytest.raises(tfe.TfeError):
         _calls.tfe_head_topk(5, 1, 13, 3, 4, 5)
