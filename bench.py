@@ -105,8 +105,8 @@ HEAD_SOURCES = ("paper_2607_07388_amd/csrc/tfe_head.hip",
 # (every kernel of the call summed), from the passes in
 # profiles/tfe_ngram_top_zipf_streams.md.
 PROFILED_TRAFFIC_BUILD = {
-    "sources_sha256": "ba8919c86fed4482f21188001dc87ab38f975b0d5aebc860104d69bb78c6eea6",
-    "bytes_per_call": 8271581751,
+    "sources_sha256": "6c050f27d661d5949cf885825dad94c23908ce16b8278fe5a18fc75a1839c0e4",
+    "bytes_per_call": 1728093718,
 }
 BUILD_SOURCES = ("paper_2607_07388_amd/csrc/tfe_build.hip",)
 
@@ -845,34 +845,12 @@ def run_head(args):
     print(json.dumps(check_line(result)))
 
 
-def build_bytes_per_window(n, vocab):
-    """Data a construction that sorts every window moves per window (what
-    `sort_gbps` prices; tfe_ngram_top sorts only the selected n-grams).  A key
-    holds 18 n bits (one more when vocab = 2^18, whose invalid-window mark
-    needs a bit above the token fields); the radix passes take 9 bits each.
-    n <= 3: the first pass forms the keys from the tokens (4 B read by its
-    histogram, 4 B read and the 8 B key written by its scatter), every later
-    pass reads the keys for its histogram (8 B) and reads and writes them in
-    its scatter (16 B); the run count reads the sorted keys twice (16 B).
-    n = 4: the low word's first pass writes key and 32-bit payload (the
-    oldest token: 4 + 4 + 12 B), its five later passes move the payload too
-    (8 + 24 B each), the passes over the high word's 18 (19) bits carry the
-    low word (4 + 24 B each), and the run count reads both words twice
-    (24 B).
-    The selection and ranking work on far fewer items."""
-    extra = 1 if vocab >= (1 << 18) else 0
-    if n <= 3:
-        passes = (18 * n + extra + 8) // 9
-        return 16 + 24 * (passes - 1) + 16
-    hi_passes = (18 + extra + 8) // 9
-    return 20 + 5 * 32 + hi_passes * 28 + 24
-
-
 def construction_bytes_per_window(n):
     """Data tfe_ngram_top moves per window of the stream: the tokens read by
     the partition's histogram and by its scatter (4 B each), the remainder
     word (4 B for n <= 2, else 8) written by the scatter and read by the
-    count.  The distinct n-grams are far fewer."""
+    count.  Not priced: the distinct n-grams, and what the count moves beyond
+    the caches where a slice has more of them than its table takes."""
     return 8 + 2 * (4 if n <= 2 else 8)
 
 
@@ -914,8 +892,7 @@ def run_build(args):
             moved = N * construction_bytes_per_window(n)
             runs.append({"stream": name, "n": n, "skip": skip, "top": top, "written": m,
                          "ms": sec * 1e3, "tokens_per_s": N / sec,
-                         "pipeline_gbps": moved / sec / 1e9,
-                         "sort_gbps": N * build_bytes_per_window(n, synth.V) / sec / 1e9})
+                         "pipeline_gbps": moved / sec / 1e9})
             print(json.dumps(runs[-1]), file=sys.stderr, flush=True)
         del tok_d
     main_run = runs[0]

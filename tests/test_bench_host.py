@@ -36,13 +36,9 @@ def test_keys_formed_counts_short_prefixes():
     assert bench.keys_formed(1, 0, 1, 2, 4) == 0
 
 
-def test_build_bytes_per_window():
-    # 36-bit 2-gram keys: four 9-bit passes; 37 bits (vocab 2^18): five.
-    assert bench.build_bytes_per_window(2, 151936) == 16 + 3 * 24 + 16
-    assert bench.build_bytes_per_window(2, 1 << 18) == 16 + 4 * 24 + 16
-    assert bench.build_bytes_per_window(4, 151936) == 20 + 5 * 32 + 2 * 28 + 24
-    assert bench.build_bytes_per_window(4, 1 << 18) == 20 + 5 * 32 + 3 * 28 + 24
-    assert bench.build_bytes_per_window(3, 151936) > bench.build_bytes_per_window(2, 151936)
+def test_construction_bytes_per_window():
+    # The tokens twice, the remainder word (4 or 8 bytes) written and read.
+    assert [bench.construction_bytes_per_window(n) for n in (1, 2, 3, 4)] == [16, 16, 24, 24]
 
 
 def test_host_cpu_fields():
