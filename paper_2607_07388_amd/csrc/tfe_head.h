@@ -65,11 +65,12 @@ bool head_fused_fits(const HeadArgs& a);
 //   K above 128: the two-launch bound from the blocks' maxima passes many tiles.
 //     K = 192, 17 rows: dim 256 34.5 / 34.5 at 80000 tokens, 39.5 / 36.6 at 100000, 45.5 / 40.3 at
 //     151936; dim 1024 63.9 / 64.5 at 100000, 74.4 / 69.6 at 128256, 79.0 / 73.7 at 151936.
-//     K = 256, 64 rows: dim 256 43.3 / 44.2 at 100000, 44.2 / 47.0 at 110000, 49.3 / 48.7 at 140000.
+//     K = 256, 64 rows: dim 256 43.3 / 44.2 at 100000, 44.2 / 47.0 at 110000, 49.3 / 48.7 at 140000;
+//     17 rows 41.4 / 38.8 at 100000.
 //   Else many rows and a large vocabulary, so that the logits' write outweighs
 //     the two grid barriers.  64 rows, K = 64: dim 256 34.1 / 35.1 at 120000, 37.2 / 36.3 at
-//     140000, 42.4 / 38.1 at 170000; dim 1024 68.3 / 68.3 at 140000, 79.8 / 76.2 at 170000.  17 rows:
-//     dim 256 32.9 / 33.0 at 140000, 34.6 / 34.0 at 151936.  One row: dim 1024 64.4 / 64.9 at 151936,
+//     140000, 42.4 / 38.1 at 170000 (K = 16: 36.1 / 34.5 at 140000);
+//     dim 1024 68.3 / 68.3 at 140000, 79.8 / 76.2 at 170000.  17 rows: dim 256 32.9 / 33.0 at 140000, 34.6 / 34.0 at 151936.  One row: dim 1024 64.4 / 64.9 at 151936,
 //     77.0 / 74.8 at 190000; dim 256 31.2 / 32.3 at 151936.
 bool head_fused_faster(const HeadArgs& a);
 // Words per (row, block) segment of the candidate scratch for this vocabulary.

@@ -612,10 +612,10 @@ __device__ __forceinline__ uint64_t select_lds(const uint64_t* c, uint32_t n, ui
 constexpr int kRowThreads = 1024;
 constexpr int kRowTiles = kHeadMaxTiles / kRowThreads;  // tile entries per thread
 constexpr int kRowCand = 16 * kHeadMaxK;                // logits of the candidate tiles
-// Candidates ranked outright (dim 256, V = 1000, K = 64, where all logits are
-// candidates: 33.2 us a call, 16.7 with the select; 4000, K = 256: 49.8 with the
-// bitonic sort that ranked more than 1024, now 23.9).
-constexpr uint32_t kRowCount = 512;
+// Candidates ranked outright; the select costs less than counting more (dim 256,
+// one row, K = 64, all logits candidates: V = 384 18.9 us a call counted; 512 19.8
+// counted, 17.4 selected; 640 24.4 and 16.5; 1000 33.2 and 17.1).
+constexpr uint32_t kRowCount = 384;
 
 // Appends the tiles whose masked key reaches lo ((key & msk) >= lo) to
 // s_tiles, in no particular order (the ranking does not depend on it): each
@@ -1525,9 +1525,10 @@ bool head_fused_fits(const HeadArgs& a) {
 }
 
 bool head_fused_faster(const HeadArgs& a) {
-  if (a.K > 128) return a.V >= (a.D == 1024 ? 8u : a.K > 192 ? 7u : 6u) << 14;
-  if (a.B > 16) return a.V >= 9u << 14;
-  return a.D == 1024 && a.V >= 11u << 14;
+  const bool wide = a.D == 1024;
+  if (a.K > 128) return a.V >= (wide ? 8u : a.K > 192 && a.B > 32 ? 7u : 6u) << 14;
+  if (a.B > 16) return a.V >= (wide || a.B <= 32 ? 9u : 8u) << 14;
+  return wide && a.V >= 11u << 14;
 }
 
 bool head_fused_resident(int D) {

@@ -64,8 +64,8 @@ class Head:
     (40000, 1024, 100, 64),    # two column groups (64 + 36 rows), ten chunks
     (151936, 1024, 64, 128),   # the backbone vocabulary, one batch-64 decode step
     (1 << 18, 256, 3, 256),    # the largest vocabulary (16384 tiles) and the largest K
-    (512, 256, 4, 32),         # as many candidates as are ranked outright, all of the logits
-    (513, 256, 4, 33),         # one more: the K largest are selected first
+    (384, 256, 4, 24),         # as many candidates as are ranked outright, all of the logits
+    (385, 256, 4, 25),         # one more: the K largest are selected first
     (1000, 512, 3, 256),
     (4080, 256, 70, 200),      # most tiles are candidates
     (4096, 1024, 5, 256),      # all of them, 4096 logits
