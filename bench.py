@@ -93,8 +93,8 @@ MULTI_SOURCES = ("paper_2607_07388_amd/csrc/tfe_multi.hip",
 # K = 128): the one-launch k_head_fused, from the passes in
 # profiles/k_head_fused_v151936_d1024_b64_k128.md.
 PROFILED_TRAFFIC_HEAD = {
-    "sources_sha256": "7b4673180138ac6e265fddd9bbf2936a9155dbb45a0f719f9ae1d65f7bc524c0",
-    "bytes_per_launch": 318459155,
+    "sources_sha256": "a9ad18b857025cfc3c599971a240ac684c372a6acb0a4e512612c83e58759269",
+    "bytes_per_launch": 318483208,
 }
 HEAD_SOURCES = ("paper_2607_07388_amd/csrc/tfe_head.hip",
                 "paper_2607_07388_amd/csrc/tfe_head.h",
